@@ -123,8 +123,8 @@ typedef enum { MDF_PERIODIC = 0, MDF_WALL = 1 } mdf_bc;
  * every step adds its fields to out[case] instead of overwriting them, in
  * the compute dtype, one rounding per step (out <- out + field(t)), so that
  * after n steps out holds the sum over the n new times (their time mean
- * times n); the caller initialises out.  Solid nodes add nothing.  Two-step
- * launches contribute both of their steps.  The selected fields of each
+ * times n); the caller initialises out.  Solid nodes add nothing.  Launches
+ * of several steps contribute each of their steps.  The selected fields of each
  * step are bitwise those of a one-step launch, so the sum is bitwise the
  * sequential sum of the per-step fields. */
 #define MDF_FIELD_ACCUMULATE 0x40u
@@ -273,16 +273,18 @@ mdf_status mdf_invariants(const mdf_ctx *ctx, int32_t case_id, double *out, void
  *   1  vector: each thread of the step kernels owns consecutive x-nodes (2
  *      for MDF_STORAGE_F64, 4 for the other storages), read and written as one
  *      16-byte (8-byte for the 16-bit storages) access per plane;
- *   2  two steps per launch (the lattices with axis links only: D2Q5, D2Q4,
- *      D3Q7, D3Q6 and their *_V forms).  2D: tiles of 64 x 4/8 nodes
- *      (FP64/other storages) take one step on the tile and a one-node halo
- *      into LDS and the second from LDS.  3D: tiles of 32 x 4 (FP64), 32 x 8
- *      (FP32) or 64 x 4 (16-bit) nodes walk a
- *      chunk of z-planes, keeping the intermediate state of three planes in
- *      LDS.  Either way the state crosses HBM once per two steps.  mdf_step,
- *      mdf_step_emit and mdf_run_steady run pairs of steps this way and the
- *      last step of each call (and of each K-step chunk) as form 0 with these
- *      bx, by; batched 3D contexts run every step as form 0.
+ *   2  several steps per launch (the lattices with axis links only: D2Q5,
+ *      D2Q4, D3Q7, D3Q6 and their *_V forms).  2D: three or four steps (five in
+ *      FP32 beyond the Infinity Cache).  FP64 grids and grids inside the
+ *      cache work in tiles that take all steps with a halo of 4 nodes; FP32
+ *      and 16-bit grids beyond it in strips of columns, walked row by row.
+ *      3D: two steps; tiles of 32 x 4 (FP64), 32 x 8 (FP32) or 64 x 8 (16-bit)
+ *      nodes walk a chunk of z-planes, keeping the intermediate state of
+ *      three planes in LDS.  Either way the state crosses HBM once per
+ *      launch.  mdf_step, mdf_step_emit and mdf_run_steady run their steps this
+ *      way but for the last one of each call (and of each K-step chunk), and
+ *      one or two before it that make no such launch, which are of form 0
+ *      with these bx, by; batched 3D contexts run every step as form 0.
  * The read kernels always use one node per thread.  Default 64 x 4, 8
  * groups, form 2 on the axis-link lattices (in 3D with FP64 and FP32
  * storage) and form 0 elsewhere; 3D axis-link lattices with 16-bit storage
@@ -334,8 +336,8 @@ mdf_status mdf_set_active(mdf_ctx *ctx, const int32_t *active);
 /* Choose the launch shape of this context by timing candidate shapes
  * (vector tiles 64x4, 128x2, 256x1, 64x2, 64x1 with XCD bands and 64x4
  * without; one-node tiles 64x4, 128x2, 256x1, 128x1, 32x8 with bands and
- * 64x4, 128x2, 128x1 without; for lattices with axis links also two steps
- * per launch with and without bands) on `trial_steps` real steps each and
+ * 64x4, 128x2, 128x1 without; for lattices with axis links also several
+ * steps per launch with and without bands) on `trial_steps` real steps each and
  * keeping the
  * fastest.  Every case advances by (trial_steps + 1) steps per candidate
  * tried (results are bitwise independent of the shape).  chosen: host

@@ -20,7 +20,7 @@ LATTICE_UNITS = ["lat_d2q5.hip", "lat_d3q7.hip", "lat_d2q5v.hip", "lat_d3q7v.hip
                  "lat_d2q9q5.hip", "lat_d3q15q7.hip"]
 SOURCES = LATTICE_UNITS + ["mdf_launch.hip", "mdf_api.cpp", "nn_kernels.hip"]
 # sources whose text determines the step kernels' machine code
-KERNEL_SOURCES = ["mdf_kernels.h", "mdf_internal.h"] + LATTICE_UNITS
+KERNEL_SOURCES = ["mdf_kernels.h", "mdf_march.h", "mdf_internal.h"] + LATTICE_UNITS
 
 # Packed-FP32 instructions are disabled for every HIP source of the project.
 # Floating-point contraction within an expression only (-ffp-contract=on): a

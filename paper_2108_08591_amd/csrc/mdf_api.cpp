@@ -6,6 +6,7 @@
 // read-back.  It never allocates device memory.
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -235,6 +236,7 @@ struct mdf_ctx {
     // batched launches (ncases > 1)
     bool batched = false;
     bool any_mask = false;
+    mdf::Cover cover = mdf::kCoverSmall; // units of launches of several steps
     mdf::BatchEntry *d_tab = nullptr;
     int *d_meta = nullptr, *d_tile_start = nullptr, *d_tile_start2 = nullptr, *d_active = nullptr;
     double *d_results = nullptr;
@@ -243,6 +245,7 @@ struct mdf_ctx {
     std::vector<double> h_results;
     int launches_since_upload = 0;       // buffer parity of the uploaded table
     int uploaded_fields = -1;
+    int batch_units = 0;                 // units of all cases in launches of several steps
     int num_cu = 0;
     std::vector<std::pair<GraphKey, hipGraphExec_t>> graphs;
     bool use_graphs = true;
@@ -343,6 +346,30 @@ mdf_status step_case(mdf_ctx *ctx, int k, bool check, uint32_t fields, void *out
     return MDF_OK;
 }
 
+// 2D axis-link lattices in form 2 run launches of several steps (k_tile, k_march).
+bool march_form(const mdf_ctx *ctx)
+{
+    return ctx->shape.fuse && lat_2d(ctx->lattice) && lat_fusable(ctx->lattice);
+}
+
+// Steps of each launch of a call of nsteps: launches of 3 .. most steps, as
+// even as they come, and one step at a time at the end, at least once, so
+// that the other buffer holds f*(t - 1) for the read kernels (and because
+// the check rides on a one-step launch).
+std::vector<int> march_split(int64_t nsteps, int most)
+{
+    std::vector<int> plan;
+    int64_t m = nsteps - 1;
+    while (m >= 3) {
+        const int64_t launches = (m + most - 1) / most;
+        const int64_t n = std::max<int64_t>(3, (m + launches - 1) / launches);
+        plan.push_back(int(n));
+        m -= n;
+    }
+    plan.insert(plan.end(), size_t(m + 1), 1);
+    return plan;
+}
+
 // Advance case k by nsteps.  With the two-step form, pairs of steps run as
 // one launch and the call always ends with at least one one-step launch, so
 // that the buffer the read kernels pull from holds f*(t - 1) again; the
@@ -350,6 +377,23 @@ mdf_status step_case(mdf_ctx *ctx, int k, bool check, uint32_t fields, void *out
 mdf_status advance_case(mdf_ctx *ctx, int k, int64_t nsteps, bool check_last, uint32_t fields, void *out,
                         hipStream_t st, int *nblocks)
 {
+    if (march_form(ctx)) {
+        for (int n : march_split(nsteps, mdf::march_max(ctx->cover, ctx->storage))) {
+            if (n == 1) {
+                nsteps -= 1;
+                mdf_status r = step_case(ctx, k, check_last && nsteps == 0, fields, out, st, nblocks);
+                if (r != MDF_OK) return r;
+                continue;
+            }
+            hipError_t e = mdf::launch_march(ctx->lattice, ctx->storage, ctx->kc[k], ctx->bufs[k], ctx->cur[k], n,
+                                             ctx->cover, fields, out, ctx->shape, st);
+            if (e != hipSuccess) return device_error(ctx, e, "launch of several steps");
+            ctx->cur[k] ^= 1;
+            ctx->time[k] += n;
+            nsteps -= n;
+        }
+        return MDF_OK;
+    }
     int64_t pairs = 0;
     if (ctx->shape.fuse && lat_fusable(ctx->lattice) && nsteps >= 3) pairs = (nsteps - 1) / 2;
     for (int64_t s = 0; s < pairs; ++s) {
@@ -407,6 +451,7 @@ mdf_status batch_upload(mdf_ctx *ctx, const std::vector<int> &active, uint32_t f
                         hipStream_t st)
 {
     const int n = ctx->ncases;
+    long long units = 0;                // of all cases, active or not
     ctx->h_tab.resize(n);
     for (int k = 0; k < n; ++k) {
         mdf::BatchEntry &e = ctx->h_tab[k];
@@ -423,11 +468,9 @@ mdf_status batch_upload(mdf_ctx *ctx, const std::vector<int> &active, uint32_t f
         e.gx = (e.p.nx + tile_x - 1) / tile_x;
         e.gy = (e.p.ny + ctx->shape.by - 1) / ctx->shape.by;
         e.ntiles = e.gx * e.gy * e.p.nz;
-        if (lat_2d(ctx->lattice)) {
-            const int rows = mdf::step2_rows(ctx->storage);
-            e.gx2 = (e.p.nx + 63) / 64;
-            e.gy2 = (e.p.ny + rows - 1) / rows;
-            e.ntiles2 = e.gx2 * e.gy2;
+        if (lat_2d(ctx->lattice) && lat_fusable(ctx->lattice)) {
+            e.march = mdf::march_plan(e.p, ctx->storage, ctx->cover);
+            units += (long long)e.march.nx * e.march.ny;
         }
         e.cur = ctx->cur[k];
         if (e.ntiles > ctx->bufs[k].max_blocks)
@@ -446,9 +489,10 @@ mdf_status batch_upload(mdf_ctx *ctx, const std::vector<int> &active, uint32_t f
     long long total2 = 0;
     for (size_t i = 0; i < active.size(); ++i) {
         ctx->h_tile_start2[i] = int(total2);
-        total2 += ctx->h_tab[active[i]].ntiles2;
+        const mdf::MarchGrid &g = ctx->h_tab[active[i]].march;
+        total2 += (long long)g.nx * g.ny;
     }
-    if (total2 > 0x7fffffffLL) return fail(ctx, MDF_EINVAL, "batch has too many tiles");
+    if (units > 0x7fffffffLL) return fail(ctx, MDF_EINVAL, "batch has too many tiles");
     ctx->h_tile_start2[active.size()] = int(total2);
     ctx->h_meta = {int(active.size()), int(total), int(total2), 0};
     hipError_t e = hipMemcpyAsync(ctx->d_tab, ctx->h_tab.data(), sizeof(mdf::BatchEntry) * n, hipMemcpyHostToDevice, st);
@@ -465,6 +509,7 @@ mdf_status batch_upload(mdf_ctx *ctx, const std::vector<int> &active, uint32_t f
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return device_error(ctx, e, "batch table upload");
+    ctx->batch_units = int(units);
     ctx->launches_since_upload = 0;
     ctx->uploaded_fields = int(fields);
     return MDF_OK;
@@ -481,6 +526,10 @@ mdf::BatchLaunch batch_args(mdf_ctx *ctx, uint32_t fields, int grid)
     bl.parity = 0;
     bl.fields = fields;
     bl.grid = grid;
+    bl.steps = 1;
+    bl.cover = ctx->cover;
+    bl.gen = false;
+    for (const KCase &p : ctx->kc) bl.gen = bl.gen || p.ffield || p.forcing != MDF_FORCING_PLAIN;
     bl.mask = ctx->any_mask;
     bl.ntstore = ctx->kc[0].ntstore != 0;   // the same for every case of a context
     bl.shape = ctx->shape;
@@ -499,29 +548,27 @@ mdf_status batch_steps(mdf_ctx *ctx, int nsteps, bool check, uint32_t fields, hi
     int grid = 0;
     mdf_status r = batch_capacity_grid(ctx, &grid);
     if (r != MDF_OK) return r;
-    const bool fuse = ctx->shape.fuse && lat_2d(ctx->lattice) && nsteps >= 3;
-    const int pairs = fuse ? (nsteps - 1) / 2 : 0;
-    const int singles = nsteps - 2 * pairs;
-    int grid2 = 0;
-    if (pairs > 0) {
-        int per_cu = 0;
-        hipError_t e = mdf::batch2_blocks_per_cu(ctx->lattice, ctx->storage, ctx->any_mask, &per_cu);
-        if (e != hipSuccess) return device_error(ctx, e, "occupancy query");
-        grid2 = ctx->num_cu * (per_cu < 1 ? 1 : per_cu);
-    }
+    const bool fuse = march_form(ctx);
+    std::vector<int> plan;                 // steps of each launch
+    if (fuse)
+        plan = march_split(nsteps, mdf::march_max(ctx->cover, ctx->storage));
+    else
+        plan.assign(nsteps, 1);
     mdf::BatchLaunch bl = batch_args(ctx, fields, grid);
-    mdf::BatchLaunch bl2 = batch_args(ctx, fields, grid2);
+    mdf::BatchLaunch blm = batch_args(ctx, fields, ctx->batch_units);
     const int p0 = ctx->launches_since_upload & 1;
+    const int launches = int(plan.size());
     auto enqueue = [&]() -> hipError_t {
         hipError_t e = hipSuccess;
-        int launch = 0;
-        for (int s = 0; s < pairs && e == hipSuccess; ++s, ++launch) {
-            bl2.parity = (p0 + launch) & 1;
-            e = mdf::launch_step2_batch(ctx->lattice, ctx->storage, bl2, st);
-        }
-        for (int s = 0; s < singles && e == hipSuccess; ++s, ++launch) {
-            bl.parity = (p0 + launch) & 1;
-            e = mdf::launch_step_batch(ctx->lattice, ctx->storage, bl, check && s == singles - 1, st);
+        for (int l = 0; l < launches && e == hipSuccess; ++l) {
+            if (plan[l] > 1) {
+                blm.parity = (p0 + l) & 1;
+                blm.steps = plan[l];
+                e = mdf::launch_march_batch(ctx->lattice, ctx->storage, blm, st);
+            } else {
+                bl.parity = (p0 + l) & 1;
+                e = mdf::launch_step_batch(ctx->lattice, ctx->storage, bl, check && l == launches - 1, st);
+            }
         }
         return e;
     };
@@ -568,7 +615,6 @@ mdf_status batch_steps(mdf_ctx *ctx, int nsteps, bool check, uint32_t fields, hi
         if (e != hipSuccess) return device_error(ctx, e, "batched step launch");
         ctx->plain_chunks += 1;
     }
-    const int launches = pairs + singles;
     ctx->launches_since_upload += launches;
     for (int k : ctx->h_active) {
         ctx->time[k] += nsteps;
@@ -711,6 +757,9 @@ mdf_status mdf_init(mdf_ctx **out, mdf_lattice lattice, mdf_storage storage, con
     for (int k = 0; k < ncases; ++k)
         pop_total += 2 * size_t(lat_planes(lattice)) * size_t(ctx->kc[k].dstride) * storage_bytes(storage);
     const size_t kInfinityCacheBytes = size_t(256) << 20;
+    long long nodes = 0;
+    for (int k = 0; k < ncases; ++k) nodes += (long long)cases[k].nx * cases[k].ny * cases[k].nz;
+    ctx->cover = mdf::march_cover(nodes, storage, pop_total > kInfinityCacheBytes);
     for (int k = 0; k < ncases; ++k) ctx->kc[k].ntstore = pop_total > kInfinityCacheBytes ? 1 : 0;
     *out = ctx;
     return MDF_OK;

@@ -67,7 +67,7 @@ struct LaunchShape {
     int bx, by;             // threads per block along x and y (bx * by <= 256)
     int groups;             // > 1: hand out tiles in `groups` contiguous bands, one per XCD
     int vx;                 // > 1: step kernels give each thread the storage's vector width of x-nodes
-    int fuse;               // 1: advance two steps per launch where possible (2D axis-link lattices)
+    int fuse;               // 1: advance several steps per launch where possible (axis-link lattices)
 };
 
 // Tile grid of one launch: gx * gy * gz tiles of bx * by threads, launched
@@ -76,6 +76,18 @@ struct LaunchShape {
 struct Tiling {
     int gx, gy, nb, groups;
     int zc = 1;
+};
+
+// How launches of several steps cover a grid: strips of columns walked row
+// by row, or tiles of one of two sizes.
+enum Cover { kCoverStrips = 0, kCoverSmall = 1, kCoverLarge = 2 };
+
+// Units of one case in launches of several steps: strips (of 64 columns,
+// `halo` of them on either side not written, `step` written) by chunks of
+// `rows` rows, or nx by ny tiles.
+struct MarchGrid {
+    int nx, ny;
+    int rows, step, halo;
 };
 
 enum ReadMode { kReadFields = 0, kReadPops = 1, kReadCheck = 2, kReadSums = 3 };
@@ -91,7 +103,7 @@ struct BatchEntry {
     double *result;
     void *out;              // emitted fields of the current call, or null
     int gx, gy, ntiles;     // tile grid of the case for the batch launch shape
-    int gx2, gy2, ntiles2;  // tile grid of two-step launches (2D axis-link lattices), else 0
+    MarchGrid march;        // units of launches of several steps (2D axis-link lattices), else zero
     int cur;                // buffer holding f*(t) when the table was uploaded
 };
 
@@ -100,11 +112,14 @@ struct BatchLaunch {
     const BatchEntry *tab;  // device table (all cases)
     const int *meta;        // device: {active cases, total tiles}
     const int *tile_start;  // device: prefix offsets of the active cases' tiles
-    const int *tile_start2; // device: the same for two-step tiles
+    const int *tile_start2; // device: the same for the units of launches of several steps
     const int *active;      // device: case ids of the active cases
     int parity;             // launches since the table upload, mod 2
     uint32_t fields;        // emitted fields (0: none)
-    int grid;               // blocks of the persistent launch
+    int grid;               // blocks of the persistent launch (one step), units of all cases (several)
+    int steps;              // steps of the launch
+    Cover cover;            // units of several steps
+    bool gen;               // any case has a force field or runs Scheme II
     bool mask;              // any case has obstacles
     bool ntstore;           // non-temporal stores and 32-bit node offsets
     LaunchShape shape;
@@ -117,14 +132,15 @@ struct LatOps {
                        void *out, LaunchShape s, hipStream_t stream);
     hipError_t (*step2)(int storage, const KCase &p, const CaseBufs &b, int src, uint32_t fields, void *out,
                         LaunchShape s, hipStream_t stream);
+    hipError_t (*march)(int storage, const KCase &p, const CaseBufs &b, int src, int steps, Cover cover, uint32_t fields,
+                        void *out, LaunchShape s, hipStream_t stream);
     hipError_t (*read)(int storage, const KCase &p, const CaseBufs &b, int src, bool pull, int mode,
                        uint32_t fields, void *out, LaunchShape s, hipStream_t stream);
     hipError_t (*init)(int storage, const KCase &p, const CaseBufs &b, int cur, int kind, const void *data,
                        hipStream_t stream);
     hipError_t (*batch)(int storage, const BatchLaunch &bl, bool check, bool emit, hipStream_t stream);
-    hipError_t (*batch2)(int storage, const BatchLaunch &bl, bool emit, hipStream_t stream);
+    hipError_t (*march_batch)(int storage, const BatchLaunch &bl, bool emit, hipStream_t stream);
     hipError_t (*batch_cap)(int storage, LaunchShape shape, bool mask, int *blocks_per_cu);
-    hipError_t (*batch2_cap)(int storage, bool mask, int *blocks_per_cu);
     hipError_t (*links)(const KCase &p, const uint8_t *solid, uint8_t *links, hipStream_t stream);
     double cs2;             // the lattice's c_s^2 (of the velocity sets, on a lattice per set)
 };
@@ -149,10 +165,15 @@ hipError_t launch_links(int lattice, const KCase &p, const uint8_t *solid, uint8
                         hipStream_t stream);
 hipError_t launch_init(int lattice, int storage, const KCase &p, const CaseBufs &b, int cur,
                        int kind, const void *data, hipStream_t stream);
-// Two steps in one launch (D2Q5, D2Q4 and their *_V forms): f*(t) in pop[src] -> f*(t+2) in
+// Two steps in one launch (D3Q7, D3Q6 and their *_V forms): f*(t) in pop[src] -> f*(t+2) in
 // pop[src ^ 1]; fields (if any) emitted at both steps.
 hipError_t launch_step2(int lattice, int storage, const KCase &p, const CaseBufs &b, int src, uint32_t fields,
                         void *out, LaunchShape shape, hipStream_t stream);
+// Several steps in one launch (3 .. march_max; the 2D lattices with axis links): f*(t) in
+// pop[src] -> f*(t + steps) in pop[src ^ 1]; fields (if any) emitted at the
+// last step, or accumulated at every step.
+hipError_t launch_march(int lattice, int storage, const KCase &p, const CaseBufs &b, int src, int steps, Cover cover,
+                        uint32_t fields, void *out, LaunchShape shape, hipStream_t stream);
 hipError_t launch_step(int lattice, int storage, const KCase &p, const CaseBufs &b, int src,
                        bool check, uint32_t fields, void *out, LaunchShape shape,
                        int *nblocks_out, hipStream_t stream);
@@ -162,11 +183,14 @@ hipError_t launch_read(int lattice, int storage, const KCase &p, const CaseBufs 
 hipError_t launch_finalize(const CaseBufs &b, int nblocks, hipStream_t stream);
 hipError_t launch_step_batch(int lattice, int storage, const BatchLaunch &bl, bool check, hipStream_t stream);
 hipError_t batch_blocks_per_cu(int lattice, int storage, LaunchShape shape, bool mask, int *blocks_per_cu);
-// Batched two steps per launch (the same lattices) over the two-step tile list.
-hipError_t launch_step2_batch(int lattice, int storage, const BatchLaunch &bl, hipStream_t stream);
-hipError_t batch2_blocks_per_cu(int lattice, int storage, bool mask, int *blocks_per_cu);
-// Two-step tile grid of a case: tiles of 64 x rows nodes.
-int step2_rows(int storage);
+// Batched launch of bl.steps steps over the list of units (the 2D lattices with axis links).
+hipError_t launch_march_batch(int lattice, int storage, const BatchLaunch &bl, hipStream_t stream);
+// Units of launches of several steps of a context with `nodes` nodes in all
+// its cases, the most steps such a launch takes (at least 3), and the units
+// of one case.
+Cover march_cover(long long nodes, int storage, bool beyond_cache);
+int march_max(Cover cover, int storage);
+MarchGrid march_plan(const KCase &p, int storage, Cover cover);
 hipError_t launch_finalize_batch(const BatchEntry *tab, const int *meta, const int *active, int nactive,
                                  hipStream_t stream);
 

@@ -116,14 +116,54 @@ int read_blocks(const KCase &p, LaunchShape s)
     return tiling_of(p, s, 1).nb;
 }
 
-int step2_rows(int storage)
+// Strips for FP32 and the 16-bit formats beyond the Infinity Cache, where
+// the traffic per step counts (4096^2: FP32 116 us per step in strips and 166
+// in tiles, FP16 99 and 125); tiles inside it (1024^2: FP32 9.8 and 8.1 us,
+// FP16 13.9 and 9.4) and for FP64 (4096^2 320 and 310 us, 1024^2 21.5 and
+// 16.8), small ones up to 49152 nodes (128^2: FP64 1.3 us per step in small and
+// 1.6 in large ones, FP32 1.2 and 1.6; 256^2: 2.5 and 2.4, 1.7 and 1.8).
+Cover march_cover(long long nodes, int storage, bool beyond_cache)
 {
-    switch (storage) {
-    case MDF_F64: return Fuse2Rows<MDF_F64>::TY;
-    case MDF_F32: return Fuse2Rows<MDF_F32>::TY;
-    case MDF_F16DEV: return Fuse2Rows<MDF_F16DEV>::TY;
-    default: return Fuse2Rows<MDF_BF16DEV>::TY;
+    if (nodes <= 49152) return kCoverSmall;
+    return storage != MDF_F64 && beyond_cache ? kCoverStrips : kCoverLarge;
+}
+
+// Four steps, in FP32 strips five (8192^2, 20 steps and a read-out: 10.4 ms
+// against 12.3 ms with four; five of the 16-bit formats spill registers).
+int march_max(Cover cover, int storage) { return cover == kCoverStrips && storage == MDF_F32 ? 5 : 4; }
+
+// Strips have one column of halo per step on either side, or, in FP32, 8:
+// 48 columns written, whose rows start and end on 64-byte blocks, so that no
+// two strips write into the same block (8192^2, five steps: 2.17 ms per pass
+// against 2.47 ms with strips of 54 columns).
+// Chunks of 16 rows, 32 in the 16-bit formats, whose wider reach per byte
+// makes the halo rows count (8192^2 FP32 10.4 ms with 16 rows, 10.7 with 32;
+// 4000 x 2977 FP16 3.36 ms with 16 and 3.16 with 32).  Longer ones, which
+// redo less, lose more by the wavefronts of a strip drifting apart: 128 rows
+// 12.9 and 3.7 ms.
+MarchGrid march_plan(const KCase &p, int storage, Cover cover)
+{
+    MarchGrid g;
+    if (cover != kCoverStrips) {
+        const bool large = cover == kCoverLarge, f64 = storage == MDF_F64;
+        const int sx = large ? TileShape<MDF_F32, true>::SX : TileShape<MDF_F32, false>::SX;
+        const int sy = !large ? TileShape<MDF_F32, false>::SY
+                              : (f64 ? TileShape<MDF_F64, true>::SY : TileShape<MDF_F32, true>::SY);
+        g.nx = (p.nx + sx - 1) / sx;
+        g.ny = (p.ny + sy - 1) / sy;
+        g.rows = g.step = g.halo = 0;
+        return g;
     }
+    const bool wallx = p.bc[0] == MDF_WALL;
+    g.halo = storage == MDF_F32 ? 8 : march_max(cover, storage);
+    g.step = 64 - 2 * g.halo;
+    g.nx = 1;
+    if (wallx ? p.nx <= 64 : (p.nx <= 64 && 64 % p.nx == 0)) g.halo = 0;
+    else if (!wallx) g.nx = (p.nx + g.step - 1) / g.step;
+    else if (p.nx - g.halo > g.step) g.nx = (p.nx - g.halo + g.step - 1) / g.step;
+    g.rows = storage == MDF_F32 ? 16 : 32;
+    g.ny = (p.ny + g.rows - 1) / g.rows;
+    return g;
 }
 
 hipError_t launch_step(int lattice, int storage, const KCase &p, const CaseBufs &b, int src, bool check,
@@ -139,8 +179,16 @@ hipError_t launch_step2(int lattice, int storage, const KCase &p, const CaseBufs
                         void *out, LaunchShape shape, hipStream_t stream)
 {
     const LatOps *o = ops_of(lattice);
-    if (!o || !axis_links(lattice) || (two_d(lattice) && p.nz != 1)) return hipErrorInvalidValue;
+    if (!o || !axis_links(lattice) || two_d(lattice)) return hipErrorInvalidValue;
     return o->step2(storage, p, b, src, fields, out, shape, stream);
+}
+
+hipError_t launch_march(int lattice, int storage, const KCase &p, const CaseBufs &b, int src, int steps, Cover cover,
+                        uint32_t fields, void *out, LaunchShape shape, hipStream_t stream)
+{
+    const LatOps *o = ops_of(lattice);
+    if (!o || !two_d(lattice) || p.nz != 1) return hipErrorInvalidValue;
+    return o->march(storage, p, b, src, steps, cover, fields, out, shape, stream);
 }
 
 hipError_t launch_read(int lattice, int storage, const KCase &p, const CaseBufs &b, int src, bool pull,
@@ -174,18 +222,11 @@ hipError_t launch_finalize(const CaseBufs &b, int nblocks, hipStream_t stream)
     return hipGetLastError();
 }
 
-hipError_t launch_step2_batch(int lattice, int storage, const BatchLaunch &bl, hipStream_t stream)
+hipError_t launch_march_batch(int lattice, int storage, const BatchLaunch &bl, hipStream_t stream)
 {
     const LatOps *o = ops_of(lattice);
     if (!o || !two_d(lattice)) return hipErrorInvalidValue;
-    return o->batch2(storage, bl, bl.fields != 0, stream);
-}
-
-hipError_t batch2_blocks_per_cu(int lattice, int storage, bool mask, int *blocks_per_cu)
-{
-    const LatOps *o = ops_of(lattice);
-    if (!o || !two_d(lattice)) return hipErrorInvalidValue;
-    return o->batch2_cap(storage, mask, blocks_per_cu);
+    return o->march_batch(storage, bl, bl.fields != 0, stream);
 }
 
 hipError_t launch_step_batch(int lattice, int storage, const BatchLaunch &bl, bool check, hipStream_t stream)
