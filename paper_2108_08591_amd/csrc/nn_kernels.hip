@@ -49,7 +49,10 @@ __device__ __forceinline__ bf16x8 zero8()
 
 // ------------------------------------------------------------------ conv fwd
 
-// LDS-staged implicit GEMM for the forward and data-gradient products.
+// LDS-staged implicit GEMM for the forward and data-gradient products, in
+// runs of 128 pixels that ignore the image's rows: for more than 32 input
+// channels, images that pixel tiles (k_conv_fwd_tile) would pad too much, and
+// outputs not aligned to 8 bytes.
 // Block: 4 waves, a 128-pixel x BN-channel output tile; wave (wm, wn) owns
 // pixels [64 wm, +64) and channels [wn BN/2, +BN/2) as 4 x (BN/32) MFMA
 // blocks of 16 x 16.  Each K step (one tap, 32 input channels) stages the
@@ -163,6 +166,119 @@ k_conv_fwd_lds(const uint16_t *__restrict__ x1, int c1, const uint16_t *__restri
             }
 }
 
+// The same products for 32 input channels from a two-dimensional pixel tile.
+// Block: 4 waves, 16 x 16 pixels of one image by BN output channels; wave v
+// owns rows [4v, +4) of the tile and all BN channels as (BN / 16) x 4 MFMA
+// blocks, the channels along M, so that a lane ends with four consecutive
+// channels of one pixel.  The block stages the 18 x 18 input pixels around the
+// tile and the weights of all nine taps (BN x 9 x 32) in LDS once and takes
+// the nine taps' products from there: an input value is read from global
+// memory 1.3 times instead of nine times, and one barrier serves 36 BN / 16
+// products per wave.  With one chunk of 32 channels the taps follow each other
+// as in k_conv_fwd_lds, so the sums are the same bits; with more, taking a
+// chunk's nine taps together would change their order.
+// 16 x 256 x 256 pixels, 32 -> 32 channels: 66 us (130 us in runs of 128 pixels),
+// bound by the latency of a block's only loads, three blocks per CU.
+constexpr int kTlPx = 18 * 18;
+
+template <int BN>
+__global__ void __launch_bounds__(256, BN == 32 ? 3 : 2)
+k_conv_fwd_tile(const uint16_t *__restrict__ x, const uint16_t *__restrict__ w, const float *__restrict__ bias, int H, int W,
+                int gx, int gy, int cout,
+                int relu, const uint16_t *__restrict__ mask, uint16_t *__restrict__ yb, float *__restrict__ yf)
+{
+    constexpr int MB = BN / 16;
+    constexpr int NA = kTlPx * 4, KA = (NA + 255) / 256;      // 16-byte chunks of input, per thread
+    constexpr int NW = 9 * BN * 4, KW = (NW + 255) / 256;     // of weights
+    __shared__ uint4 sA4[kTlPx * kCvLd / 8];
+    __shared__ uint4 sW4[9 * BN * kCvLd / 8];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int i = lane & 15, g = lane >> 4;
+    const int b = blockIdx.x / (gx * gy), tile = blockIdx.x % (gx * gy);
+    const int tx0 = (tile % gx) * 16, ty0 = (tile / gx) * 16;
+    const int co0 = blockIdx.y * BN;
+    uint4 ra[KA], rw[KW];
+#pragma unroll
+    for (int r = 0; r < KA; ++r) {
+        const int idx = t + 256 * r;
+        const int px = idx >> 2, ch = idx & 3;
+        const int yy = ty0 - 1 + px / 18, xx = tx0 - 1 + px % 18;
+        ra[r] = uint4{0u, 0u, 0u, 0u};
+        if (idx < NA && yy >= 0 && yy < H && xx >= 0 && xx < W)
+            ra[r] = *reinterpret_cast<const uint4 *>(x + (((long long)b * H + yy) * W + xx) * 32 + 8 * ch);
+    }
+#pragma unroll
+    for (int r = 0; r < KW; ++r) {
+        const int idx = t + 256 * r;
+        rw[r] = uint4{0u, 0u, 0u, 0u};
+        if (NW % 256 == 0 || idx < NW)
+            rw[r] = *reinterpret_cast<const uint4 *>(w + ((long long)(co0 + (idx >> 2) % BN) * 9 + (idx >> 2) / BN) * 32 +
+                                                    8 * (idx & 3));
+    }
+#pragma unroll
+    for (int r = 0; r < KA; ++r) {
+        const int idx = t + 256 * r;
+        if (idx < NA) sA4[(idx >> 2) * (kCvLd / 8) + (idx & 3)] = ra[r];
+    }
+#pragma unroll
+    for (int r = 0; r < KW; ++r) {
+        const int idx = t + 256 * r;
+        if (NW % 256 == 0 || idx < NW) sW4[(idx >> 2) * (kCvLd / 8) + (idx & 3)] = rw[r];
+    }
+    f32x4 acc[MB][4];
+    const uint16_t *sA = reinterpret_cast<const uint16_t *>(sA4), *sW = reinterpret_cast<const uint16_t *>(sW4);
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int n = 0; n < 4; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    __syncthreads();
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+        const int dy = tap / 3, dx = tap % 3;
+        bf16x8 fw[MB], fx[4];
+#pragma unroll
+        for (int m = 0; m < MB; ++m) fw[m] = load8(sW + (tap * BN + 16 * m + i) * kCvLd + 8 * g);
+#pragma unroll
+        for (int n = 0; n < 4; ++n) fx[n] = load8(sA + ((4 * wave + n + dy) * 18 + i + dx) * kCvLd + 8 * g);
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int n = 0; n < 4; ++n)
+                acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[m], fx[n], acc[m][n], 0, 0, 0);
+    }
+    const int xx = tx0 + i;
+    if (xx >= W) return;
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        const int yy = ty0 + 4 * wave + n;
+        if (yy >= H) continue;
+        const long long base = (((long long)b * H + yy) * W + xx) * cout + co0 + 4 * g;
+#pragma unroll
+        for (int m = 0; m < MB; ++m) {
+            uint16_t vm[4] = {0, 0, 0, 0}, vb[4];
+            float v[4];
+            if (mask) {
+                const uint2 q = *reinterpret_cast<const uint2 *>(mask + base + 16 * m);
+                __builtin_memcpy(vm, &q, 8);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                v[r] = acc[m][n][r];
+                if (bias) v[r] += bias[co0 + 16 * m + 4 * g + r];
+                if (relu && !(v[r] > 0.f)) v[r] = 0.f;
+                if (mask && !(bf2f(vm[r]) > 0.f)) v[r] = 0.f;
+                vb[r] = f2bf(v[r]);
+            }
+            if (yb) {
+                uint2 q;
+                __builtin_memcpy(&q, vb, 8);
+                *reinterpret_cast<uint2 *>(yb + base + 16 * m) = q;
+            }
+            if (yf) *reinterpret_cast<float4 *>(yf + base + 16 * m) = float4{v[0], v[1], v[2], v[3]};
+        }
+    }
+}
+
 // wt[ci][tap][co] = w[co][8 - tap][ci]
 __global__ void __launch_bounds__(256) k_flip(const uint16_t *__restrict__ w, int cout, int cin, uint16_t *__restrict__ wt)
 {
@@ -179,35 +295,78 @@ __global__ void __launch_bounds__(256) k_flip(const uint16_t *__restrict__ w, in
 
 constexpr int kWgBlocks = 1024;    // target blocks of one weight-gradient launch
 
+// LDS tiles of the weight gradient, [pixel row][C channels] without padding:
+// the 32-byte groups of 16 channels of a row are permuted by the row (an
+// exclusive or), so that the eight rows r, .. r + 3 and r + 8, .. r + 11 that
+// half a wavefront reads at once lie in distinct banks for any r.
+template <int C>
+__device__ __forceinline__ int swz(int row)
+{
+    return C == 64 ? ((row >> 1) & 1) | ((row >> 2) & 2) : (row >> 3) & 1;
+}
+
+// 16-byte chunk c8 of a row, as an index of such chunks.
+template <int C>
+__device__ __forceinline__ int chunk_at(int row, int c8)
+{
+    return row * (C / 8) + (c8 ^ (swz<C>(row) << 1));
+}
+
+// Rows r, .. r + 3, channels 16 grp .. 16 grp + 15, transposed: the lane gets its
+// channel (lane % 16) of the four rows.  Each lane of a group of 16 addresses
+// 8 of the group's 128 bytes, the read hands them out by column.
+template <int C>
+__device__ __forceinline__ uint2 rows4(const uint16_t *p, int r, int grp, int i)
+{
+    typedef short s4 __attribute__((ext_vector_type(4)));
+    using L4 = __attribute__((address_space(3))) s4;
+    const int row = r + (i >> 2);
+    const s4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((L4 *)(p + row * C + 16 * (grp ^ swz<C>(row)) + 4 * (i & 3)));
+    return __builtin_bit_cast(uint2, v);
+}
+
+// MFMA operand of the 32 pixels from row r on and 16 channels: K index 8 g + j
+// is pixel 8 g + j.
+template <int C>
+__device__ __forceinline__ bf16x8 rows32(const uint16_t *p, int r, int grp, int i, int g)
+{
+    const uint2 a = rows4<C>(p, r + 8 * g, grp, i), b = rows4<C>(p, r + 8 * g + 4, grp, i);
+    return __builtin_bit_cast(bf16x8, uint4{a.x, a.y, b.x, b.y});
+}
+
 // Weight gradient with all nine taps in one block.  The K dimension (pixels)
 // is walked in segments of 32 consecutive pixels of one image row; per
-// segment the block stages, transposed to [channel][pixel] in LDS so that
-// every MFMA operand is one 16-byte read, the output-gradient row segment
-// (MT channels) once and the input window of rows y-1..y+1 (NT channels)
-// in three copies shifted by dx = -1, 0, +1, and takes the products of all
-// nine taps from them: each dy value is read from global memory once per
-// block instead of once per tap.  Wave (wm, wn) owns channels
-// [wm MT/2, +MT/2) x [wn NT/2, +NT/2) of every tap.  Pixels beyond the row
-// end contribute zero (their dy is staged as zero); input pixels outside the
-// image are zero.  Segments [s0, s1) of split blockIdx.z; partial sums per
-// split are reduced in a fixed order by k_wgrad_reduce.
+// segment the block stages the output-gradient row segment (MT channels)
+// and the input window of rows y-1..y+1 and 34 pixels (NT channels) in LDS as
+// they lie in memory, [pixel][channel], and takes the products of all nine
+// taps from there with the transposing LDS read: a tap is an offset of whole
+// rows.  Two LDS buffers, one barrier per segment, the next segment's global loads in flight during the
+// products.  NT = 64: wave v owns all MT output channels by input channels
+// [16 v, +16); NT = 32: waves (wm, wn) own halves of MT by 16.  Pixels beyond
+// the row end contribute zero (their dy is staged as zero); input pixels
+// outside the image are zero.  Segments [s0, s1) of split blockIdx.z; partial
+// sums per split are reduced in a fixed order by k_wgrad_reduce.
+// Bound by the products and, behind them, the LDS reads (26 of 8 bytes per
+// lane for 36 products).  16 x 128 x 128 pixels, 192 -> 64 channels: 332 us when
+// the tiles were staged transposed, value by value, in three shifted copies,
+// 135 us now (430 TFLOP/s).
 template <int MT, int NT>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, 2)
 k_conv_wgrad9(const uint16_t *__restrict__ x1, int c1, const uint16_t *__restrict__ x2, int c2,
               const uint16_t *__restrict__ dyp, int B, int H, int W, int cout, int nsplit,
               float *__restrict__ partial, float *__restrict__ bpart)
 {
-    constexpr int MB = MT / 32, NB = NT / 32;
-    constexpr int LD = 40;                              // row: 32 pixels + 8 pad
+    constexpr int MB = (NT == 64) ? MT / 16 : MT / 32;
     constexpr int NDY = 32 * MT / 8;                    // 16-byte dy chunks per segment
     constexpr int NX = 3 * 34 * NT / 8;                 // 16-byte input chunks per window
     constexpr int KX = (NX + 255) / 256;
-    __shared__ uint16_t ys[MT * LD];
-    __shared__ uint16_t xw[9 * NT * LD];                // [dx + 1][row][ci][pixel]
+    __shared__ uint4 ys4[2][32 * MT / 8];
+    __shared__ uint4 xw4[2][3 * 34 * NT / 8];
     const int cin = c1 + c2;
     const int co0 = blockIdx.x * MT, ci0 = blockIdx.y * NT;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int i = lane & 15, g = lane >> 4, wm = wave >> 1, wn = wave & 1;
+    const int i = lane & 15, g = lane >> 4;
+    const int wm = (NT == 64) ? 0 : wave >> 1, wn = (NT == 64) ? wave : wave & 1;
     const uint16_t *src = (ci0 < c1) ? x1 : x2;
     const int cs = (ci0 < c1) ? c1 : c2;
     const int cc = (ci0 < c1) ? ci0 : ci0 - c1;
@@ -215,13 +374,11 @@ k_conv_wgrad9(const uint16_t *__restrict__ x1, int c1, const uint16_t *__restric
     const long long nseg = (long long)B * H * S;
     const long long per = (nseg + nsplit - 1) / nsplit;
     const long long s0 = blockIdx.z * per, s1 = (s0 + per < nseg) ? s0 + per : nseg;
-    f32x4 acc[9][MB][NB];
+    f32x4 acc[9][MB];
 #pragma unroll
     for (int k = 0; k < 9; ++k)
 #pragma unroll
-        for (int a = 0; a < MB; ++a)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) acc[k][a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int a = 0; a < MB; ++a) acc[k][a] = f32x4{0.f, 0.f, 0.f, 0.f};
     uint4 rdy, rx[KX];
     // bias gradient (blocks of the first input-channel tile): the thread that
     // stages dy chunk (pixel j, channels 8 c8 ..) sums those channels over the
@@ -252,13 +409,11 @@ k_conv_wgrad9(const uint16_t *__restrict__ x1, int c1, const uint16_t *__restric
             }
         }
     };
-    auto stash = [&]() __attribute__((always_inline)) {
+    auto stash = [&](int buf) __attribute__((always_inline)) {
         if (t < NDY) {
-            const int j = t / (MT / 8), c8 = t % (MT / 8);
-            const uint16_t *u = reinterpret_cast<const uint16_t *>(&rdy);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) ys[(8 * c8 + e) * LD + j] = u[e];
+            ys4[buf][chunk_at<MT>(t / (MT / 8), t % (MT / 8))] = rdy;
             if (bias) {
+                const uint16_t *u = reinterpret_cast<const uint16_t *>(&rdy);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) bacc[e] += bf2f(u[e]);
             }
@@ -266,58 +421,46 @@ k_conv_wgrad9(const uint16_t *__restrict__ x1, int c1, const uint16_t *__restric
 #pragma unroll
         for (int r = 0; r < KX; ++r) {
             const int idx = t + 256 * r;
-            if (idx >= NX) continue;
-            const int wr = idx / (34 * NT / 8), rem = idx % (34 * NT / 8);
-            const int c = rem / (NT / 8), c8 = rem % (NT / 8);
-            const uint16_t *u = reinterpret_cast<const uint16_t *>(&rx[r]);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {               // copy d holds x[xs + j + d - 1]
-                const int j = c + 1 - d - 1 + 0;        // pixel c of the window is xs - 1 + c
-                if (j < 0 || j >= 32) continue;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) xw[((d * 3 + wr) * NT + 8 * c8 + e) * LD + j] = u[e];
-            }
+            if (idx < NX) xw4[buf][chunk_at<NT>(idx / (NT / 8), idx % (NT / 8))] = rx[r];
         }
     };
-    if (s0 < s1) fetch(s0);
+    if (s0 < s1) {
+        fetch(s0);
+        stash(0);
+    }
+    __syncthreads();
     for (long long sg = s0; sg < s1; ++sg) {
-        __syncthreads();                                // the previous segment's reads are done
-        stash();
-        __syncthreads();
+        const int buf = (int)(sg - s0) & 1;
         if (sg + 1 < s1) fetch(sg + 1);
+        const uint16_t *ys = reinterpret_cast<const uint16_t *>(ys4[buf]);
+        const uint16_t *xw = reinterpret_cast<const uint16_t *>(xw4[buf]);
         bf16x8 fa[MB];
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-            fa[mb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(&ys[(wm * (MT / 2) + 16 * mb + i) * LD + 8 * g]));
+        for (int mb = 0; mb < MB; ++mb) fa[mb] = rows32<MT>(ys, 0, wm * (MT / 32) + mb, i, g);
 #pragma unroll
         for (int tap = 0; tap < 9; ++tap) {
-            const int wr = tap / 3, d = tap % 3;        // dy = wr - 1, dx = d - 1
+            const bf16x8 fb = rows32<NT>(xw, (tap / 3) * 34 + tap % 3, wn, i, g);     // dy = tap / 3 - 1, dx = tap % 3 - 1
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const bf16x8 fb = __builtin_bit_cast(
-                    bf16x8, *reinterpret_cast<const uint4 *>(&xw[((d * 3 + wr) * NT + wn * (NT / 2) + 16 * nb + i) * LD + 8 * g]));
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-                    acc[tap][mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[mb], fb, acc[tap][mb][nb], 0, 0, 0);
-            }
+            for (int mb = 0; mb < MB; ++mb)
+                acc[tap][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[mb], fb, acc[tap][mb], 0, 0, 0);
         }
+        if (sg + 1 < s1) stash(buf ^ 1);
+        __syncthreads();
     }
 #pragma unroll
     for (int tap = 0; tap < 9; ++tap)
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int co = co0 + wm * (MT / 2) + 16 * mb + 4 * g + r;
-                    const int ci = ci0 + wn * (NT / 2) + 16 * nb + i;
-                    partial[(((long long)blockIdx.z * cout + co) * 9 + tap) * cin + ci] = acc[tap][mb][nb][r];
-                }
+            for (int r = 0; r < 4; ++r) {
+                const int co = co0 + wm * (MT / 2) + 16 * mb + 4 * g + r;
+                const int ci = ci0 + 16 * wn + i;
+                partial[(((long long)blockIdx.z * cout + co) * 9 + tap) * cin + ci] = acc[tap][mb][r];
+            }
     if (bias) {
-        __syncthreads();                                // xw is free: reuse it as [pixel slot][co] floats
-        float *red = reinterpret_cast<float *>(xw);
-        static_assert(32 * MT * sizeof(float) <= sizeof(xw), "bias slots fit the input window");
+        // the window is free (a barrier ends the loop): reuse it as [pixel slot][co] floats
+        float *red = reinterpret_cast<float *>(&xw4[0][0]);
+        static_assert(32 * MT * sizeof(float) <= sizeof(xw4), "bias slots fit the input window");
         if (t < NDY) {
             const int j = t / (MT / 8), c8 = t % (MT / 8);
 #pragma unroll
@@ -334,103 +477,170 @@ k_conv_wgrad9(const uint16_t *__restrict__ x1, int c1, const uint16_t *__restric
 
 // Sums of split partials: out[g][k] = sum of partial[sp][k] over the splits
 // sp of group g = blockIdx.y ([g chunk, (g + 1) chunk)), added in split
-// order.  One group (chunk >= nsplit) gives the final sums; with several, a
+// order, for the n weights and, in the same launch, the nb biases (nb = 0:
+// none).  One group (chunk >= nsplit) gives the final sums; with several, a
 // second pass over the group sums adds them in group order, so the result
 // is the same fixed-order sum whatever the launch.
 __global__ void __launch_bounds__(256)
-k_wgrad_reduce(const float *__restrict__ partial, long long n, int nsplit, int chunk, float *__restrict__ out)
+k_wgrad_reduce(const float *__restrict__ partial, long long n, const float *__restrict__ bpart, int nb, int nsplit,
+               int chunk, float *__restrict__ out, float *__restrict__ bout)
 {
     const int g = blockIdx.y;
     const int sp0 = g * chunk, sp1 = (sp0 + chunk < nsplit) ? sp0 + chunk : nsplit;
-    for (long long k = blockIdx.x * 256LL + threadIdx.x; k < n; k += (long long)gridDim.x * 256) {
+    for (long long k = blockIdx.x * 256LL + threadIdx.x; k < n + nb; k += (long long)gridDim.x * 256) {
+        const bool w = k < n;
+        const float *src = w ? partial + k : bpart + (k - n);
+        const long long stride = w ? n : nb;
         float s = 0.f;
-        for (int sp = sp0; sp < sp1; ++sp) s += partial[sp * n + k];
-        out[g * n + k] = s;
+#pragma unroll 8
+        for (int sp = sp0; sp < sp1; ++sp) s += src[sp * stride];
+        if (w) out[g * n + k] = s;
+        else bout[(long long)g * nb + (k - n)] = s;
     }
 }
 
 // ------------------------------------------------------------------ elementwise
 
+// The elementwise kernels move NC channels per thread: 8 (one 16-byte access
+// per operand) where the channels and every pointer allow it, else 1.  They
+// are bound by memory; one value per thread left them bound by the index
+// arithmetic (upsampling 16 x 128 x 128 x 64 to 256 x 256: 113 us a value at a
+// time).
+template <int NC> struct Bf;
+template <> struct Bf<1> {
+    uint16_t v[1];
+    static __device__ __forceinline__ Bf load(const uint16_t *p) { return {{*p}}; }
+    __device__ __forceinline__ void store(uint16_t *p) const { *p = v[0]; }
+};
+template <> struct Bf<8> {
+    uint16_t v[8];
+    static __device__ __forceinline__ Bf load(const uint16_t *p)
+    {
+        return __builtin_bit_cast(Bf, *reinterpret_cast<const uint4 *>(p));
+    }
+    __device__ __forceinline__ void store(uint16_t *p) const
+    {
+        *reinterpret_cast<uint4 *>(p) = __builtin_bit_cast(uint4, *this);
+    }
+};
+
+// Chunk k of [B][H][W][C]: its place and channel.
+template <int NC>
+struct Place {
+    int b, y, x, c;
+    __device__ __forceinline__ Place(long long k, int H, int W, int C)
+    {
+        const uint32_t cn = uint32_t(C) / NC;
+        uint64_t q = uint64_t(k);
+        if (q >> 32 == 0) {
+            uint32_t r = uint32_t(q);
+            c = int(r % cn) * NC;
+            r /= cn;
+            x = int(r % uint32_t(W));
+            r /= uint32_t(W);
+            y = int(r % uint32_t(H));
+            b = int(r / uint32_t(H));
+        } else {
+            c = int(q % cn) * NC;
+            q /= cn;
+            x = int(q % uint32_t(W));
+            q /= uint32_t(W);
+            y = int(q % uint32_t(H));
+            b = int(q / uint32_t(H));
+        }
+    }
+    __device__ __forceinline__ long long at(int yy, int xx, int H, int W, int C) const
+    {
+        return (((long long)b * H + yy) * W + xx) * C + c;
+    }
+};
+
+template <int NC>
 __global__ void __launch_bounds__(256)
 k_avgpool2_fwd(const uint16_t *__restrict__ x, int B, int H, int W, int C, uint16_t *__restrict__ y)
 {
     const int Ho = H / 2, Wo = W / 2;
-    const long long n = (long long)B * Ho * Wo * C;
+    const long long n = (long long)B * Ho * Wo * C / NC;
     for (long long k = blockIdx.x * 256LL + threadIdx.x; k < n; k += (long long)gridDim.x * 256) {
-        const int c = (int)(k % C);
-        long long q = k / C;
-        const int j = (int)(q % Wo);
-        q /= Wo;
-        const int i = (int)(q % Ho);
-        const int b = (int)(q / Ho);
-        const long long base = (((long long)b * H + 2 * i) * W + 2 * j) * C + c;
-        const float s = bf2f(x[base]) + bf2f(x[base + C]) + bf2f(x[base + (long long)W * C]) +
-                        bf2f(x[base + (long long)W * C + C]);
-        y[k] = f2bf(0.25f * s);
+        const Place<NC> q(k, Ho, Wo, C);
+        const long long base = q.at(2 * q.y, 2 * q.x, H, W, C);
+        const Bf<NC> a = Bf<NC>::load(x + base), b = Bf<NC>::load(x + base + C),
+                     c = Bf<NC>::load(x + base + (long long)W * C), d = Bf<NC>::load(x + base + (long long)W * C + C);
+        Bf<NC> o;
+#pragma unroll
+        for (int e = 0; e < NC; ++e)
+            o.v[e] = f2bf(0.25f * (bf2f(a.v[e]) + bf2f(b.v[e]) + bf2f(c.v[e]) + bf2f(d.v[e])));
+        o.store(y + k * NC);
     }
 }
 
+template <int NC>
 __global__ void __launch_bounds__(256)
 k_avgpool2_bwd(const uint16_t *__restrict__ dy, int B, int H, int W, int C, uint16_t *__restrict__ dx)
 {
-    const long long n = (long long)B * H * W * C;
-    const int Ho = H / 2, Wo = W / 2;
+    const long long n = (long long)B * H * W * C / NC;
     for (long long k = blockIdx.x * 256LL + threadIdx.x; k < n; k += (long long)gridDim.x * 256) {
-        const int c = (int)(k % C);
-        long long q = k / C;
-        const int xx = (int)(q % W);
-        q /= W;
-        const int yy = (int)(q % H);
-        const int b = (int)(q / H);
-        dx[k] = f2bf(0.25f * bf2f(dy[(((long long)b * Ho + yy / 2) * Wo + xx / 2) * C + c]));
+        const Place<NC> q(k, H, W, C);
+        const Bf<NC> a = Bf<NC>::load(dy + q.at(q.y / 2, q.x / 2, H / 2, W / 2, C));
+        Bf<NC> o;
+#pragma unroll
+        for (int e = 0; e < NC; ++e) o.v[e] = f2bf(0.25f * bf2f(a.v[e]));
+        o.store(dx + k * NC);
     }
 }
 
+template <int NC>
 __global__ void __launch_bounds__(256)
 k_upsample2_fwd(const uint16_t *__restrict__ x, int B, int H, int W, int C, uint16_t *__restrict__ y)
 {
     const int H2 = 2 * H, W2 = 2 * W;
-    const long long n = (long long)B * H2 * W2 * C;
+    const long long n = (long long)B * H2 * W2 * C / NC;
     for (long long k = blockIdx.x * 256LL + threadIdx.x; k < n; k += (long long)gridDim.x * 256) {
-        const int c = (int)(k % C);
-        long long q = k / C;
-        const int xx = (int)(q % W2);
-        q /= W2;
-        const int yy = (int)(q % H2);
-        const int b = (int)(q / H2);
-        y[k] = x[(((long long)b * H + yy / 2) * W + xx / 2) * C + c];
+        const Place<NC> q(k, H2, W2, C);
+        Bf<NC>::load(x + q.at(q.y / 2, q.x / 2, H, W, C)).store(y + k * NC);
     }
 }
 
+template <int NC>
 __global__ void __launch_bounds__(256)
 k_upsample2_bwd(const uint16_t *__restrict__ dy, int B, int H, int W, int C, uint16_t *__restrict__ dx)
 {
     const int W2 = 2 * W;
-    const long long n = (long long)B * H * W * C;
+    const long long n = (long long)B * H * W * C / NC;
     for (long long k = blockIdx.x * 256LL + threadIdx.x; k < n; k += (long long)gridDim.x * 256) {
-        const int c = (int)(k % C);
-        long long q = k / C;
-        const int j = (int)(q % W);
-        q /= W;
-        const int i = (int)(q % H);
-        const int b = (int)(q / H);
-        const long long base = (((long long)b * 2 * H + 2 * i) * W2 + 2 * j) * C + c;
-        const float s = bf2f(dy[base]) + bf2f(dy[base + C]) + bf2f(dy[base + (long long)W2 * C]) +
-                        bf2f(dy[base + (long long)W2 * C + C]);
-        dx[k] = f2bf(s);
+        const Place<NC> q(k, H, W, C);
+        const long long base = q.at(2 * q.y, 2 * q.x, 2 * H, W2, C);
+        const Bf<NC> a = Bf<NC>::load(dy + base), b = Bf<NC>::load(dy + base + C),
+                     c = Bf<NC>::load(dy + base + (long long)W2 * C), d = Bf<NC>::load(dy + base + (long long)W2 * C + C);
+        Bf<NC> o;
+#pragma unroll
+        for (int e = 0; e < NC; ++e) o.v[e] = f2bf(bf2f(a.v[e]) + bf2f(b.v[e]) + bf2f(c.v[e]) + bf2f(d.v[e]));
+        o.store(dx + k * NC);
     }
 }
 
+template <int NC>
 __global__ void __launch_bounds__(256)
 k_add(const uint16_t *a, const uint16_t *b, const uint16_t *mask, long long n, uint16_t *out)
 {
+    n /= NC;
     for (long long k = blockIdx.x * 256LL + threadIdx.x; k < n; k += (long long)gridDim.x * 256) {
-        float v = bf2f(a[k]);
-        if (b) v += bf2f(b[k]);
-        if (mask && !(bf2f(mask[k]) > 0.f)) v = 0.f;
-        out[k] = f2bf(v);
+        const Bf<NC> va = Bf<NC>::load(a + k * NC);
+        Bf<NC> vb = va, vm = va, o;
+        if (b) vb = Bf<NC>::load(b + k * NC);
+        if (mask) vm = Bf<NC>::load(mask + k * NC);
+#pragma unroll
+        for (int e = 0; e < NC; ++e) {
+            float v = bf2f(va.v[e]);
+            if (b) v += bf2f(vb.v[e]);
+            if (mask && !(bf2f(vm.v[e]) > 0.f)) v = 0.f;
+            o.v[e] = f2bf(v);
+        }
+        o.store(out + k * NC);
     }
 }
+
+bool aligned16(const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 
 // ------------------------------------------------------------------ 1x1 head
 
@@ -493,17 +703,132 @@ k_head_bwd_w(const uint16_t *__restrict__ x, const float *__restrict__ dy, int P
     }
 }
 
+// Sum of the block partials of one of the cin cout + cout values per block,
+// in block order: the threads bring 1024 partials at a time to LDS, the first
+// adds them up (a thread per value reading them one by one waited for memory
+// at every addition: 474 us for 2048 partials).
 __global__ void __launch_bounds__(256)
 k_head_bwd_reduce(const float *__restrict__ partial, int nblk, int cin, int cout, float *__restrict__ dw,
                   float *__restrict__ db)
 {
-    const int t = threadIdx.x;
+    __shared__ float part[1024];
+    const int t = threadIdx.x, k = blockIdx.x;
     const int nw = cout * cin;
-    if (t >= nw + cout) return;
     float s = 0.f;
-    for (int b = 0; b < nblk; ++b) s += partial[(long long)b * (nw + cout) + t];
-    if (t < nw) dw[t] = s;
-    else if (db) db[t - nw] = s;
+    for (int b0 = 0; b0 < nblk; b0 += 1024) {
+        const int m = nblk - b0 < 1024 ? nblk - b0 : 1024;
+        __syncthreads();
+        for (int b = t; b < m; b += 256) part[b] = partial[(long long)(b0 + b) * (nw + cout) + k];
+        __syncthreads();
+        if (t == 0) {
+#pragma unroll 16
+            for (int b = 0; b < m; ++b) s += part[b];
+        }
+    }
+    if (t == 0) {
+        if (k < nw) dw[k] = s;
+        else if (db) db[k - nw] = s;
+    }
+}
+
+// The head for 32 input channels and at most 8 output channels (the
+// network's), pixels read and written 16 bytes at a time; the FP32 rows of
+// cout values pass through LDS, so that they are contiguous in memory too.
+// The kernels above cover every other size.  Bound by memory: at 2^20 pixels
+// and 7 outputs the backward pass takes 64 + 64 MB in and 64 MB out.
+constexpr int kHeadC = 32, kHeadO = 8;
+
+__global__ void __launch_bounds__(256)
+k_head_fwd32(const uint16_t *__restrict__ x, int P, const float *__restrict__ w, const float *__restrict__ bias, int cout,
+             float *__restrict__ y)
+{
+    __shared__ float sw[kHeadO * kHeadC];
+    __shared__ float sb[kHeadO];
+    __shared__ float sy[256 * kHeadO];
+    const int t = threadIdx.x;
+    for (int k = t; k < cout * kHeadC; k += 256) sw[k] = w[k];
+    if (t < cout) sb[t] = bias ? bias[t] : 0.f;
+    __syncthreads();
+    const long long p0 = blockIdx.x * 256LL, p = p0 + t;
+    if (p < P) {
+        Bf<8> xv[kHeadC / 8];
+#pragma unroll
+        for (int q = 0; q < kHeadC / 8; ++q) xv[q] = Bf<8>::load(x + p * kHeadC + 8 * q);
+        for (int o = 0; o < cout; ++o) {
+            float s = sb[o];
+#pragma unroll
+            for (int c = 0; c < kHeadC; ++c) s += sw[o * kHeadC + c] * bf2f(xv[c / 8].v[c % 8]);
+            sy[t * cout + o] = s;
+        }
+    }
+    __syncthreads();
+    const int m = int((P - p0 < 256 ? P - p0 : 256)) * cout;
+    for (int k = t; k < m; k += 256) y[p0 * cout + k] = sy[k];
+}
+
+// dx: 64 pixels per block, a thread per pixel and 8 channels.
+__global__ void __launch_bounds__(256)
+k_head_bwd_x32(const float *__restrict__ dy, int P, const float *__restrict__ w, int cout,
+               const uint16_t *__restrict__ mask, uint16_t *__restrict__ dx)
+{
+    __shared__ float sw[kHeadO * kHeadC];
+    __shared__ float sd[64 * kHeadO];
+    const int t = threadIdx.x;
+    const long long p0 = blockIdx.x * 64LL, p = p0 + t / 4;
+    for (int k = t; k < cout * kHeadC; k += 256) sw[k] = w[k];
+    const int m = int((P - p0 < 64 ? P - p0 : 64)) * cout;
+    for (int k = t; k < m; k += 256) sd[k] = dy[p0 * cout + k];
+    __syncthreads();
+    if (p >= P) return;
+    const int c0 = (t % 4) * 8;
+    float s[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s[e] = 0.f;
+    for (int o = 0; o < cout; ++o) {
+        const float d = sd[(t / 4) * cout + o];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[e] += d * sw[o * kHeadC + c0 + e];
+    }
+    Bf<8> vm, r;
+    if (mask) vm = Bf<8>::load(mask + p * kHeadC + c0);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        if (mask && !(bf2f(vm.v[e]) > 0.f)) s[e] = 0.f;
+        r.v[e] = f2bf(s[e]);
+    }
+    r.store(dx + p * kHeadC + c0);
+}
+
+// Partial dw and db of kHeadRows pixels per block, a thread per (o, c) pair
+// and per o for the bias, as k_head_bwd_w and in its order, from LDS copies of
+// the pixels that all threads bring in with 16-byte loads.
+constexpr int kHeadRows = 512;
+
+__global__ void __launch_bounds__(256)
+k_head_bwd_w32(const uint16_t *__restrict__ x, const float *__restrict__ dy, int P, int cout, float *__restrict__ partial)
+{
+    __shared__ uint4 sx4[kHeadRows * kHeadC / 8];
+    __shared__ float sd[kHeadRows * (kHeadO - 1)];
+    const int t = threadIdx.x;
+    const int nw = cout * kHeadC;
+    const long long r0 = (long long)blockIdx.x * kHeadRows;
+    const int rows = (int)(P - r0 < kHeadRows ? P - r0 : kHeadRows);
+    for (int k = t; k < rows * (kHeadC / 8); k += 256)
+        sx4[k] = *reinterpret_cast<const uint4 *>(x + r0 * kHeadC + 8 * k);
+    for (int k = t; k < rows * cout; k += 256) sd[k] = dy[r0 * cout + k];
+    __syncthreads();
+    const uint16_t *sx = reinterpret_cast<const uint16_t *>(sx4);
+    float s = 0.f;
+    if (t < nw) {
+        const int o = t / kHeadC, c = t % kHeadC;
+#pragma unroll 8
+        for (int p = 0; p < rows; ++p) s += sd[p * cout + o] * bf2f(sx[p * kHeadC + c]);
+    } else if (t < nw + cout) {
+        const int o = t - nw;
+#pragma unroll 8
+        for (int p = 0; p < rows; ++p) s += sd[p * cout + o];
+    }
+    if (t < nw + cout) partial[(long long)blockIdx.x * (nw + cout) + t] = s;
 }
 
 // ------------------------------------------------------------------ loss, optimiser
@@ -623,6 +948,18 @@ using namespace mdfnn;
 
 extern "C" {
 
+// Pixel tiles (k_conv_fwd_tile) where they cover the images with little
+// waste, or are few enough for one round of the chip, whose length then
+// counts and not the padding: 16 x 256 x 256 pixels, 32 -> 32 channels 66 us
+// against 130 in runs of 128 pixels; but 16 x 9 x 1000 (1.8 times padded, 1008
+// tiles) 21 against 19.
+static bool conv_tiles_pay(int B, int H, int W, int cout)
+{
+    const long long tiles = (long long)B * ((H + 15) / 16) * ((W + 15) / 16);
+    const long long blocks = tiles * (cout % 64 == 0 ? cout / 64 : cout / 32);
+    return blocks <= 512 || tiles * 256 * 5 <= 8LL * B * H * W;
+}
+
 int mdfnn_conv3x3_fwd(const uint16_t *x1, int c1, const uint16_t *x2, int c2, const uint16_t *w,
                       const float *bias, int B, int H, int W, int cout, int relu, const uint16_t *mask,
                       uint16_t *y_bf16, float *y_f32, void *stream)
@@ -633,6 +970,19 @@ int mdfnn_conv3x3_fwd(const uint16_t *x1, int c1, const uint16_t *x2, int c2, co
     if (M > (1LL << 31)) return MDFNN_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const unsigned gx = (unsigned)((M + kCvBM - 1) / kCvBM);
+    const int tgx = (W + 15) / 16, tgy = (H + 15) / 16;
+    const bool wide = (reinterpret_cast<uintptr_t>(mask) % 8 == 0) && (reinterpret_cast<uintptr_t>(y_bf16) % 8 == 0) &&
+                      (reinterpret_cast<uintptr_t>(y_f32) % 16 == 0);
+    if (wide && c1 + c2 == 32 && conv_tiles_pay(B, H, W, cout)) {
+        const unsigned nt = (unsigned)tgx * tgy * B;
+        if (cout % 64 == 0)
+            hipLaunchKernelGGL(k_conv_fwd_tile<64>, dim3(nt, cout / 64), dim3(256), 0, st, x1, w, bias, H, W,
+                               tgx, tgy, cout, relu, mask, y_bf16, y_f32);
+        else
+            hipLaunchKernelGGL(k_conv_fwd_tile<32>, dim3(nt, cout / 32), dim3(256), 0, st, x1, w, bias, H, W,
+                               tgx, tgy, cout, relu, mask, y_bf16, y_f32);
+        return status(hipGetLastError());
+    }
     if (cout % 128 == 0)
         hipLaunchKernelGGL(k_conv_fwd_lds<128>, dim3(gx, cout / 128), dim3(256), 0, st, x1, c1, x2, c2, w, bias, B, H,
                            W, cout, relu, mask, y_bf16, y_f32);
@@ -672,17 +1022,21 @@ static int wgrad_splits(int B, int H, int W, int ntiles)
 // Splits per group of the first reduction pass.
 constexpr int kWgChunk = 32;
 
-// Fixed-order sum over ns split partials of n values each (two passes when
-// ns > kWgChunk, through mid: ceil(ns / kWgChunk) * n floats).
-static hipError_t reduce_splits(const float *partial, long long n, int ns, float *mid, float *out, hipStream_t st)
+// Fixed-order sum over ns split partials of n weights and nb biases (two
+// passes when ns > kWgChunk, through mid: ceil(ns / kWgChunk) * (n + nb) floats).
+static hipError_t reduce_splits(const float *partial, long long n, const float *bpart, int nb, int ns, float *mid,
+                                float *out, float *bout, hipStream_t st)
 {
     if (ns <= kWgChunk) {
-        hipLaunchKernelGGL(k_wgrad_reduce, dim3(grid1(n), 1), dim3(256), 0, st, partial, n, ns, ns, out);
+        hipLaunchKernelGGL(k_wgrad_reduce, dim3(grid1(n + nb), 1), dim3(256), 0, st, partial, n, bpart, nb, ns, ns, out,
+                           bout);
         return hipGetLastError();
     }
     const int G = (ns + kWgChunk - 1) / kWgChunk;
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(grid1(n), G), dim3(256), 0, st, partial, n, ns, kWgChunk, mid);
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(grid1(n), 1), dim3(256), 0, st, mid, n, G, G, out);
+    float *bmid = mid + (size_t)G * n;
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3(grid1(n + nb), G), dim3(256), 0, st, partial, n, bpart, nb, ns, kWgChunk, mid,
+                       bmid);
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3(grid1(n + nb), 1), dim3(256), 0, st, mid, n, bmid, nb, G, G, out, bout);
     return hipGetLastError();
 }
 
@@ -725,17 +1079,18 @@ int mdfnn_conv3x3_wgrad(const uint16_t *x1, int c1, const uint16_t *x2, int c2, 
     if (e != hipSuccess) return MDFNN_EDEVICE;
     const long long n = (long long)cout * 9 * cin;
     float *mid = wpart + (size_t)ns * (n + cout);
-    e = reduce_splits(wpart, n, ns, mid, dw, st);
-    if (e != hipSuccess) return MDFNN_EDEVICE;
-    if (db) e = reduce_splits(bpart, cout, ns, mid + (size_t)((ns + kWgChunk - 1) / kWgChunk) * n, db, st);
-    return status(e);
+    return status(reduce_splits(wpart, n, bpart, db ? cout : 0, ns, mid, dw, db, st));
 }
 
 int mdfnn_avgpool2_fwd(const uint16_t *x, int B, int H, int W, int C, uint16_t *y, void *stream)
 {
     if (!x || !y || B < 1 || H < 2 || W < 2 || H % 2 || W % 2 || C < 1) return MDFNN_EINVAL;
     const long long n = (long long)B * (H / 2) * (W / 2) * C;
-    hipLaunchKernelGGL(k_avgpool2_fwd, dim3(grid1(n)), dim3(256), 0, static_cast<hipStream_t>(stream), x, B, H, W, C, y);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (C % 8 == 0 && aligned16(x) && aligned16(y))
+        hipLaunchKernelGGL(k_avgpool2_fwd<8>, dim3(grid1(n / 8)), dim3(256), 0, st, x, B, H, W, C, y);
+    else
+        hipLaunchKernelGGL(k_avgpool2_fwd<1>, dim3(grid1(n)), dim3(256), 0, st, x, B, H, W, C, y);
     return status(hipGetLastError());
 }
 
@@ -743,7 +1098,11 @@ int mdfnn_avgpool2_bwd(const uint16_t *dy, int B, int H, int W, int C, uint16_t 
 {
     if (!dy || !dx || B < 1 || H < 2 || W < 2 || H % 2 || W % 2 || C < 1) return MDFNN_EINVAL;
     const long long n = (long long)B * H * W * C;
-    hipLaunchKernelGGL(k_avgpool2_bwd, dim3(grid1(n)), dim3(256), 0, static_cast<hipStream_t>(stream), dy, B, H, W, C, dx);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (C % 8 == 0 && aligned16(dy) && aligned16(dx))
+        hipLaunchKernelGGL(k_avgpool2_bwd<8>, dim3(grid1(n / 8)), dim3(256), 0, st, dy, B, H, W, C, dx);
+    else
+        hipLaunchKernelGGL(k_avgpool2_bwd<1>, dim3(grid1(n)), dim3(256), 0, st, dy, B, H, W, C, dx);
     return status(hipGetLastError());
 }
 
@@ -751,7 +1110,11 @@ int mdfnn_upsample2_fwd(const uint16_t *x, int B, int H, int W, int C, uint16_t 
 {
     if (!x || !y || B < 1 || H < 1 || W < 1 || C < 1) return MDFNN_EINVAL;
     const long long n = (long long)B * 4 * H * W * C;
-    hipLaunchKernelGGL(k_upsample2_fwd, dim3(grid1(n)), dim3(256), 0, static_cast<hipStream_t>(stream), x, B, H, W, C, y);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (C % 8 == 0 && aligned16(x) && aligned16(y))
+        hipLaunchKernelGGL(k_upsample2_fwd<8>, dim3(grid1(n / 8)), dim3(256), 0, st, x, B, H, W, C, y);
+    else
+        hipLaunchKernelGGL(k_upsample2_fwd<1>, dim3(grid1(n)), dim3(256), 0, st, x, B, H, W, C, y);
     return status(hipGetLastError());
 }
 
@@ -759,14 +1122,22 @@ int mdfnn_upsample2_bwd(const uint16_t *dy, int B, int H, int W, int C, uint16_t
 {
     if (!dy || !dx || B < 1 || H < 1 || W < 1 || C < 1) return MDFNN_EINVAL;
     const long long n = (long long)B * H * W * C;
-    hipLaunchKernelGGL(k_upsample2_bwd, dim3(grid1(n)), dim3(256), 0, static_cast<hipStream_t>(stream), dy, B, H, W, C, dx);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (C % 8 == 0 && aligned16(dy) && aligned16(dx))
+        hipLaunchKernelGGL(k_upsample2_bwd<8>, dim3(grid1(n / 8)), dim3(256), 0, st, dy, B, H, W, C, dx);
+    else
+        hipLaunchKernelGGL(k_upsample2_bwd<1>, dim3(grid1(n)), dim3(256), 0, st, dy, B, H, W, C, dx);
     return status(hipGetLastError());
 }
 
 int mdfnn_add(const uint16_t *a, const uint16_t *b, const uint16_t *mask, long long n, uint16_t *out, void *stream)
 {
     if (!a || !out || n < 0) return MDFNN_EINVAL;
-    hipLaunchKernelGGL(k_add, dim3(grid1(n)), dim3(256), 0, static_cast<hipStream_t>(stream), a, b, mask, n, out);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (n % 8 == 0 && aligned16(a) && aligned16(b) && aligned16(mask) && aligned16(out))
+        hipLaunchKernelGGL(k_add<8>, dim3(grid1(n / 8)), dim3(256), 0, st, a, b, mask, n, out);
+    else
+        hipLaunchKernelGGL(k_add<1>, dim3(grid1(n)), dim3(256), 0, st, a, b, mask, n, out);
     return status(hipGetLastError());
 }
 
@@ -774,14 +1145,18 @@ int mdfnn_head_fwd(const uint16_t *x, int P, int cin, const float *w, const floa
                    void *stream)
 {
     if (!x || !w || !y || P < 1 || cin < 1 || cin > 32 || cout < 1 || cout > 32) return MDFNN_EINVAL;
-    hipLaunchKernelGGL(k_head_fwd, dim3((P + 255) / 256), dim3(256), 0, static_cast<hipStream_t>(stream), x, P, cin, w,
-                       bias, cout, y);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const int nblk = (int)(((long long)P + 255) / 256);
+    if (cin == kHeadC && cout <= kHeadO && aligned16(x))
+        hipLaunchKernelGGL(k_head_fwd32, dim3(nblk), dim3(256), 0, st, x, P, w, bias, cout, y);
+    else
+        hipLaunchKernelGGL(k_head_fwd, dim3(nblk), dim3(256), 0, st, x, P, cin, w, bias, cout, y);
     return status(hipGetLastError());
 }
 
 size_t mdfnn_head_scratch_bytes(int P, int cin, int cout)
 {
-    const int rows = 512;
+    const int rows = kHeadRows;
     const size_t nblk = (size_t)((P + rows - 1) / rows);
     return nblk * (size_t)(cin * cout + cout) * sizeof(float) + 256;
 }
@@ -793,13 +1168,18 @@ int mdfnn_head_bwd(const uint16_t *x, const float *dy, int P, int cin, const flo
         cin * cout + cout > 256)
         return MDFNN_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (dx)
+    const bool fast = cin == kHeadC && cout <= kHeadO;
+    if (dx && fast && aligned16(dx) && aligned16(mask))
+        hipLaunchKernelGGL(k_head_bwd_x32, dim3((int)(((long long)P + 63) / 64)), dim3(256), 0, st, dy, P, w, cout, mask, dx);
+    else if (dx)
         hipLaunchKernelGGL(k_head_bwd_x, dim3((P + 255) / 256), dim3(256), 0, st, dy, P, cin, w, cout, mask, dx);
-    const int rows = 512;
+    const int rows = kHeadRows;
     const int nblk = (P + rows - 1) / rows;
     float *part = static_cast<float *>(scratch);
-    hipLaunchKernelGGL(k_head_bwd_w, dim3(nblk), dim3(256), 0, st, x, dy, P, cin, cout, rows, part);
-    hipLaunchKernelGGL(k_head_bwd_reduce, dim3(1), dim3(256), 0, st, part, nblk, cin, cout, dw, db);
+    // (cin cout + cout <= 256: at most 7 outputs)
+    if (fast && aligned16(x)) hipLaunchKernelGGL(k_head_bwd_w32, dim3(nblk), dim3(256), 0, st, x, dy, P, cout, part);
+    else hipLaunchKernelGGL(k_head_bwd_w, dim3(nblk), dim3(256), 0, st, x, dy, P, cin, cout, rows, part);
+    hipLaunchKernelGGL(k_head_bwd_reduce, dim3(cin * cout + cout), dim3(256), 0, st, part, nblk, cin, cout, dw, db);
     return status(hipGetLastError());
 }
 
