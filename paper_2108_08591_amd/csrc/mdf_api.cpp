@@ -40,13 +40,22 @@ bool lat_diag(int lattice) { return (lattice & 8) != 0; }
 // two steps per launch: lattices with axis links (2D tiles, or 3D tiles
 // walking z-planes)
 bool lat_fusable(int lattice) { return !lat_diag(lattice); }
-// the default form: two steps per launch on the axis-link lattices, except
-// 3D with 16-bit storage (measured slower there than one node per thread)
-bool lat_fused_default(int lattice, int storage)
+// the default form: several steps per launch on the axis-link lattices.  In 3D
+// two steps per launch pay on large grids that their tiles (32 x 4 nodes of a
+// plane in FP64, 32 x 8 in FP32) cover with little waste; below, a block that
+// walks a chunk of planes leaves most of the chip idle (per step, two and one
+// per launch: 64^3 34 and 18 us in FP64, 29 and 11 in FP32; 96^3 80 and 82, 33 and
+// 31; 128^3 168 and 174, 74 and 89; 130 x 97 x 75, 1.3 times padded, 127 and 92, 58
+// and 40; 33 x 200 x 200, 1.9 times, 304 and 180, 144 and 133).  The 16-bit formats
+// run one step per launch at every size (256^3 346 and 331 us, 64^3 36 and 8).
+bool lat_fused_default(int lattice, int storage, const mdf_case &c)
 {
     if (lat_diag(lattice)) return false;
     if (lat_2d(lattice)) return true;
-    return storage == MDF_F64 || storage == MDF_F32;
+    if (storage != MDF_F64 && storage != MDF_F32) return false;
+    const int64_t ty = storage == MDF_F64 ? 4 : 8;
+    const int64_t covered = ((c.nx + 31) / 32 * 32) * ((c.ny + ty - 1) / ty * ty), plane = int64_t(c.nx) * c.ny;
+    return plane * c.nz >= (storage == MDF_F64 ? 800000 : 1000000) && covered * 20 <= plane * 23;
 }
 int lat_d(int lattice) { return lat_2d(lattice) ? 2 : 3; }
 int lat_q(int lattice)
@@ -690,13 +699,17 @@ mdf_status mdf_init(mdf_ctx **out, mdf_lattice lattice, mdf_storage storage, con
 
     mdf_ctx *ctx = new mdf_ctx;
     ctx->lattice = lattice;
-    ctx->shape.fuse = lat_fused_default(lattice, storage) ? 1 : 0;
+    ctx->shape.fuse = lat_fused_default(lattice, storage, cases[0]) ? 1 : 0;
     if (!lat_2d(lattice) && !lat_diag(lattice) && (storage == MDF_F16DEV || storage == MDF_BF16DEV)) {
         // one step per launch in 3D: 128 x 2 blocks without XCD bands ran
         // 0-3 % faster than 64 x 4 with bands at 128^3 and 9-12 % at 256^3
-        // and 384^3 (D3Q7, FP16 and BF16)
-        ctx->shape.bx = 128;
-        ctx->shape.by = 2;
+        // and 384^3 (D3Q7, FP16 and BF16); 64 x 4, without bands as well,
+        // where rows of 64 threads waste less of the last block (per step
+        // 160^3 100 us against 115, 192^3 145 against 169)
+        const int nx = cases[0].nx;
+        const bool narrow = nx > 128 && (nx + 63) / 64 * 64 < (nx + 127) / 128 * 128;
+        ctx->shape.bx = narrow ? 64 : 128;
+        ctx->shape.by = narrow ? 4 : 2;
         ctx->shape.groups = 1;
     }
     ctx->storage = storage;
