@@ -50,9 +50,8 @@ __device__ __forceinline__ bf16x8 zero8()
 // ------------------------------------------------------------------ conv fwd
 
 // LDS-staged implicit GEMM for the forward and data-gradient products, in
-// runs of 128 pixels that ignore the image's rows: for more than 32 input
-// channels, images that pixel tiles (k_conv_fwd_tile) would pad too much, and
-// outputs not aligned to 8 bytes.
+// runs of 128 pixels that ignore the image's rows: where its wide blocks pay
+// (mdfnn_conv3x3_fwd), and for outputs not aligned to 8 bytes.
 // Block: 4 waves, a 128-pixel x BN-channel output tile; wave (wm, wn) owns
 // pixels [64 wm, +64) and channels [wn BN/2, +BN/2) as 4 x (BN/32) MFMA
 // blocks of 16 x 16.  Each K step (one tap, 32 input channels) stages the
@@ -166,6 +165,145 @@ k_conv_fwd_lds(const uint16_t *__restrict__ x1, int c1, const uint16_t *__restri
             }
 }
 
+// Four consecutive output channels at k: bias, ReLU, mask, then BF16 (8-byte
+// stores) or FP32 (16).
+__device__ __forceinline__ void conv_out(const f32x4 &acc, const float *__restrict__ bias, int relu,
+                                         const uint16_t *__restrict__ mask, uint16_t *__restrict__ yb,
+                                         float *__restrict__ yf, long long k)
+{
+    uint16_t vm[4] = {0, 0, 0, 0}, vb[4];
+    float v[4];
+    if (mask) {
+        const uint2 q = *reinterpret_cast<const uint2 *>(mask + k);
+        __builtin_memcpy(vm, &q, 8);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        v[r] = acc[r];
+        if (bias) v[r] += bias[r];
+        if (relu && !(v[r] > 0.f)) v[r] = 0.f;
+        if (mask && !(bf2f(vm[r]) > 0.f)) v[r] = 0.f;
+        vb[r] = f2bf(v[r]);
+    }
+    if (yb) {
+        uint2 q;
+        __builtin_memcpy(&q, vb, 8);
+        *reinterpret_cast<uint2 *>(yb + k) = q;
+    }
+    if (yf) *reinterpret_cast<float4 *>(yf + k) = float4{v[0], v[1], v[2], v[3]};
+}
+
+// The same products in smaller blocks, more of them per CU: 4 waves, two along
+// the pixels (a run of 128) and two along BN output channels, the channels
+// along M, so that a lane ends with four consecutive channels of a pixel,
+// written as 8 bytes.  Rows of the LDS tiles are not padded: their 16-byte
+// chunks are permuted by the row, so that eight consecutive rows' reads of one
+// chunk lie in distinct banks; 24 KB (BN = 64) leave room for six blocks, whose
+// products cover each other's barriers and loads.  Whether a tap of a staged
+// pixel lies inside the image is a bit of a mask formed once.  The chunks of a
+// tap follow each other and the taps as in k_conv_fwd_lds: the sums are the
+// same bits.  (K steps of 64 channels, or 64 x 64 products per wave, need fewer
+// barriers and LDS reads but leave two blocks per CU: 16 x 128 x 128 pixels, 192
+// -> 64 channels 189 and 206 us, against 153 as it is.)
+__device__ __forceinline__ int conv_chunk(int row, int c) { return row * 4 + (c ^ ((row >> 2) & 3)); }
+
+template <int BN>
+__global__ void __launch_bounds__(256)
+k_conv_fwd_run(const uint16_t *__restrict__ x1, int c1, const uint16_t *__restrict__ x2, int c2,
+               const uint16_t *__restrict__ w, const float *__restrict__ bias, int B, int H, int W, int cout, int relu,
+               const uint16_t *__restrict__ mask, uint16_t *__restrict__ yb, float *__restrict__ yf)
+{
+    constexpr int PX = 128, MB = BN / 32, CH = 4;
+    constexpr int KA = PX * CH / 256, KW = (BN * CH + 255) / 256, RS = 256 / CH;     // rows a pass of the block stages
+    __shared__ uint4 sA4[2][PX * CH];
+    __shared__ uint4 sB4[2][BN * CH];
+    const int cin = c1 + c2;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int i = lane & 15, g = lane >> 4, wm = wave & 1, wn = wave >> 1;
+    const long long M = (long long)B * H * W;
+    const long long pbase = (long long)blockIdx.x * PX;
+    const int co0 = blockIdx.y * BN;
+    const int ch = t % CH, row0 = t / CH;
+    long long pix[KA];              // pixel index of each staged row
+    unsigned inside[KA];            // bit tap: the tap's pixel lies in the image
+#pragma unroll
+    for (int r = 0; r < KA; ++r) {
+        const long long p = pbase + row0 + RS * r;
+        const long long pp = p < M ? p : 0;
+        const int rem = (int)(pp % ((long long)H * W));
+        const int y = rem / W, x = rem % W;
+        pix[r] = pp;
+        inside[r] = 0;
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap) {
+            const int yy = y + tap / 3 - 1, xx = x + tap % 3 - 1;
+            if (p < M && yy >= 0 && yy < H && xx >= 0 && xx < W) inside[r] |= 1u << tap;
+        }
+    }
+    const int nk = 9 * (cin / 32);
+    uint4 ra[KA], rw[KW];
+    int tap = 0, c0 = 0;            // of the next step to fetch
+    auto fetch = [&]() __attribute__((always_inline)) {
+        const bool first = c0 < c1;
+        const uint16_t *src = first ? x1 : x2;
+        const int cs = first ? c1 : c2, cc = first ? c0 : c0 - c1;
+        const int shift = (tap / 3 - 1) * W + tap % 3 - 1;
+#pragma unroll
+        for (int r = 0; r < KA; ++r) {
+            ra[r] = uint4{0u, 0u, 0u, 0u};
+            if ((inside[r] >> tap) & 1u)
+                ra[r] = *reinterpret_cast<const uint4 *>(src + (pix[r] + shift) * cs + cc + 8 * ch);
+        }
+        const uint16_t *wk = w + (long long)tap * cin + c0 + 8 * ch;
+#pragma unroll
+        for (int r = 0; r < KW; ++r)
+            if (BN * CH % 256 == 0 || row0 + RS * r < BN)
+                rw[r] = *reinterpret_cast<const uint4 *>(wk + (long long)(co0 + row0 + RS * r) * 9 * cin);
+        c0 += 32;
+        if (c0 == cin) { c0 = 0; ++tap; }
+    };
+    auto stash = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < KA; ++r) sA4[buf][conv_chunk(row0 + RS * r, ch)] = ra[r];
+#pragma unroll
+        for (int r = 0; r < KW; ++r)
+            if (BN * CH % 256 == 0 || row0 + RS * r < BN) sB4[buf][conv_chunk(row0 + RS * r, ch)] = rw[r];
+    };
+    f32x4 acc[MB][4];
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int n = 0; n < 4; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    fetch();
+    stash(0);
+    __syncthreads();
+    for (int ks = 0; ks < nk; ++ks) {
+        const int buf = ks & 1;
+        if (ks + 1 < nk) fetch();
+        bf16x8 fw[MB], fx[4];
+#pragma unroll
+        for (int m = 0; m < MB; ++m) fw[m] = __builtin_bit_cast(bf16x8, sB4[buf][conv_chunk((wn * MB + m) * 16 + i, g)]);
+#pragma unroll
+        for (int n = 0; n < 4; ++n) fx[n] = __builtin_bit_cast(bf16x8, sA4[buf][conv_chunk(wm * 64 + 16 * n + i, g)]);
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int n = 0; n < 4; ++n)
+                acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[m], fx[n], acc[m][n], 0, 0, 0);
+        if (ks + 1 < nk) stash(buf ^ 1);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        const long long p = pbase + wm * 64 + 16 * n + i;
+        if (p >= M) continue;
+        const long long base = p * cout + co0 + wn * MB * 16 + 4 * g;
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+            conv_out(acc[m][n], bias ? bias + co0 + (wn * MB + m) * 16 + 4 * g : nullptr, relu, mask, yb, yf, base + 16 * m);
+    }
+}
+
 // The same products for 32 input channels from a two-dimensional pixel tile.
 // Block: 4 waves, 16 x 16 pixels of one image by BN output channels; wave v
 // owns rows [4v, +4) of the tile and all BN channels as (BN / 16) x 4 MFMA
@@ -254,28 +392,8 @@ k_conv_fwd_tile(const uint16_t *__restrict__ x, const uint16_t *__restrict__ w, 
         if (yy >= H) continue;
         const long long base = (((long long)b * H + yy) * W + xx) * cout + co0 + 4 * g;
 #pragma unroll
-        for (int m = 0; m < MB; ++m) {
-            uint16_t vm[4] = {0, 0, 0, 0}, vb[4];
-            float v[4];
-            if (mask) {
-                const uint2 q = *reinterpret_cast<const uint2 *>(mask + base + 16 * m);
-                __builtin_memcpy(vm, &q, 8);
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                v[r] = acc[m][n][r];
-                if (bias) v[r] += bias[co0 + 16 * m + 4 * g + r];
-                if (relu && !(v[r] > 0.f)) v[r] = 0.f;
-                if (mask && !(bf2f(vm[r]) > 0.f)) v[r] = 0.f;
-                vb[r] = f2bf(v[r]);
-            }
-            if (yb) {
-                uint2 q;
-                __builtin_memcpy(&q, vb, 8);
-                *reinterpret_cast<uint2 *>(yb + base + 16 * m) = q;
-            }
-            if (yf) *reinterpret_cast<float4 *>(yf + base + 16 * m) = float4{v[0], v[1], v[2], v[3]};
-        }
+        for (int m = 0; m < MB; ++m)
+            conv_out(acc[m][n], bias ? bias + co0 + 16 * m + 4 * g : nullptr, relu, mask, yb, yf, base + 16 * m);
     }
 }
 
@@ -981,6 +1099,23 @@ int mdfnn_conv3x3_fwd(const uint16_t *x1, int c1, const uint16_t *x2, int c2, co
         else
             hipLaunchKernelGGL(k_conv_fwd_tile<32>, dim3(nt, cout / 32), dim3(256), 0, st, x1, w, bias, H, W,
                                tgx, tgy, cout, relu, mask, y_bf16, y_f32);
+        return status(hipGetLastError());
+    }
+    // Runs in small blocks (k_conv_fwd_run), 32 channels wide where 64 would
+    // leave the chip half empty, and k_conv_fwd_lds where its wider blocks win:
+    // long sums over many blocks of 128 channels, and many blocks of 32
+    // (us, k_conv_fwd_lds / 64 wide / 32 wide: 16 x 128 x 128, 192 -> 64: 156 / 153 /
+    // 293; 16 x 32 x 32, 256 -> 256: 67 / 55 / 58; 1 x 32 x 32, 256 -> 256: 65 / 45 / 36;
+    // 16 x 64 x 64, 384 -> 128: 111 / 119 / 209; 16 x 256 x 256, 96 -> 32: 193 / - / 195).
+    const long long runs = gx;
+    const bool lds = cout % 64 != 0 ? runs * (cout / 32) > 512 : cout % 128 == 0 && c1 + c2 > 256 && runs * (cout / 128) >= 512;
+    if (wide && !lds) {
+        if (cout % 64 == 0 && runs * (cout / 64) > 256)
+            hipLaunchKernelGGL(k_conv_fwd_run<64>, dim3(gx, cout / 64), dim3(256), 0, st, x1, c1, x2, c2, w, bias, B, H, W,
+                               cout, relu, mask, y_bf16, y_f32);
+        else
+            hipLaunchKernelGGL(k_conv_fwd_run<32>, dim3(gx, cout / 32), dim3(256), 0, st, x1, c1, x2, c2, w, bias, B, H, W,
+                               cout, relu, mask, y_bf16, y_f32);
         return status(hipGetLastError());
     }
     if (cout % 128 == 0)

@@ -32,7 +32,9 @@ def _rel(ref, got):
 # rows and columns; the last two take the kernel without pixel tiles (more
 # than 512 blocks, padded more than 1.6 times)
 CONV = [(1, 16, 16, 32, 0, 32), (2, 15, 17, 32, 32, 64), (1, 1, 40, 64, 0, 96), (2, 33, 1, 64, 64, 64),
-        (1, 31, 65, 96, 32, 32), (3, 8, 9, 32, 96, 192), (41, 3, 200, 32, 0, 64), (33, 17, 129, 32, 32, 32)]
+        (1, 31, 65, 96, 32, 32), (3, 8, 9, 32, 96, 192), (41, 3, 200, 32, 0, 64), (33, 17, 129, 32, 32, 32),
+        # runs of 128 pixels, 64 channels wide, and the widest blocks (384 input channels, 512 blocks)
+        (2, 129, 128, 64, 0, 64), (1, 256, 257, 256, 128, 128)]
 
 
 @pytest.mark.parametrize("shape", CONV)
