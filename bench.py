@@ -6,7 +6,7 @@ channels, N x N with N in {64, 96, ..., 512}, Re log-uniform in [10, 1000],
 lid or centreline speed in [0.05, 0.1]; 53.6 M nodes), D2Q5 with three
 distribution sets (ubar_0, u, v), FP64 storage (the paper's arithmetic),
 halfway anti-bounce-back walls; all cases advance together in one
-persistent batched launch per step (two steps per launch where the
+persistent batched launch per step (several steps per launch where the
 autotuner picks that form), and every 100 steps the FP64 K-interval
 residual of every case is evaluated inside the last step of the chunk and
 read back (the loop of a steady solve).  A step is one pass of all of that
@@ -213,7 +213,7 @@ def summarize_traffic(fetch_db, write_db, copy_fetch_db, copy_write_db, kernel_p
 def parse_launch(text):
     """'128x2g8t' -> (128, 2, 8, 2): tile of 128 x 2 threads, 8 XCD bands and
     the step-kernel form: 's' one node per thread (default, 0), 'v' vector
-    (1), 't' two steps per launch (2)."""
+    (1), 't' several steps per launch (2)."""
     t = text.lower()
     form = 0
     if t[-1] in "svt":
@@ -249,7 +249,7 @@ def time_launches(solver, stream, n, fields=0, out=None, reps=3):
 
 def variants_study(out_path):
     """Cost of each variant of the update against the plain one on the same
-    grid, storage and default launch shape (two steps per launch on the 2D
+    grid, storage and default launch shape (several steps per launch on the 2D
     axis-link lattices, one node per thread elsewhere),
     stepping without field emission: the d velocity sets only (Remark IV),
     Scheme II forcing (eq. 2-3c), and a per-node force field (d more reads
@@ -1070,11 +1070,20 @@ def _launch_ms(solver, stream, nsteps, reps=5):
     return statistics.median(res)
 
 
+def several_steps(storage, state_bytes):
+    """Steps per launch and kernel of the 2D form with several steps per
+    launch, for a context whose two population buffers hold `state_bytes`:
+    tiles of four steps in FP64 and inside the 256 MB Infinity Cache, strips
+    of five (FP32) or four steps beyond it."""
+    strips = storage != "f64" and state_bytes > 256 << 20
+    return (5 if strips and storage == "f32" else 4), ("k_march" if strips else "k_tile")
+
+
 def batch_headline(args, dev, stream):
     """The headline: the seeded 512-case uneven batch (2D cavities and
     channels, N in {64, 96, ..., 512}, 53.6 M nodes, the largest
     configuration that fits one GPU) in the paper's FP64, one persistent
-    launch per step (two steps per launch where the autotuner picks it), with
+    launch per step (several steps per launch where the autotuner picks it), with
     the FP64 K-interval residual fused into the last step of every 100."""
     import torch
     from paper_2108_08591_amd import cases as C
@@ -1109,17 +1118,17 @@ def batch_headline(args, dev, stream):
     mlups = nodes * args.steps / elapsed / 1e6
 
     # average launch duration of the dominant kernel, HIP events on its
-    # stream: a call of 2m + 1 steps is m two-step launches and one one-step
-    # launch (a chunk graph), a call of 1 step one one-step launch
+    # stream: a call of 201 steps is 200 / s launches of s steps and one
+    # one-step launch (a chunk graph), a call of 1 step one one-step launch
     step_bytes = 2 * 5 * nsets * sbytes            # one read and one write of the state per node and step
     if form == 2:
-        m = 100
-        t_long = _launch_ms(solver, stream, 2 * m + 1)
+        steps_per_launch, kname = several_steps(args.storage, nodes * step_bytes)
+        m = 200 // steps_per_launch
+        t_long = _launch_ms(solver, stream, 201)
         t_one = _launch_ms(solver, stream, 1)
         avg_ms = (t_long - t_one) / m
-        steps_per_launch = 2
-        kernel = f"k_step2_batch<D2Q5{'' if nsets == 3 else 'V'},{args.storage.upper()}>"
-        timing = f"HIP events, (time of {2 * m + 1} steps - time of 1 step) / {m}, median of 5"
+        kernel = f"{kname}_batch<D2Q5{'' if nsets == 3 else 'V'},{args.storage.upper()}>"
+        timing = f"HIP events, (time of 201 steps - time of 1 step) / {m}, median of 5"
     else:
         avg_ms = _launch_ms(solver, stream, 200) / 200
         steps_per_launch = 1
@@ -1173,8 +1182,8 @@ def batch_headline(args, dev, stream):
             "hbm_physical": {"bytes_per_launch": phys_bytes, "achieved": round(phys, 1),
                              "frac": round(phys / HBM_PEAK_GBS, 4)},
             "note": ("achieved counts the per-step algorithmic bytes (one read and one write of the state per "
-                     "node-step) of every node-step a launch performs; with two steps per launch the state "
-                     "crosses HBM once per two steps, so frac may exceed 1; hbm_physical counts one read and "
+                     "node-step) of every node-step a launch performs; with several steps per launch the state "
+                     "crosses HBM once per launch, so frac may exceed 1; hbm_physical counts one read and "
                      f"one write of the state per launch; working set {2 * phys_bytes / 2 ** 30:.1f} GiB"),
         },
         "residual_median": float(sorted(res)[len(res) // 2]),
@@ -1207,13 +1216,13 @@ def cavity_leg(args, dev, stream, N, nsteps):
     mlups = spec.nodes * nsteps / (ev0.elapsed_time(ev1) / 1e3) / 1e6
     state_bytes = 2 * 5 * nsets * 4
     field_bytes = 4 * 4
-    steps_per_launch = 2 if form == 2 else 1
+    steps_per_launch, kname = several_steps("f32", spec.nodes * state_bytes) if form == 2 else (1, "k_step")
     nt = 201 if form == 2 else 200
     avg_ms = time_launches(solver, stream, nt if N <= 2048 else 41, fields, out, 5) * steps_per_launch
     alg_bytes = spec.nodes * (state_bytes + field_bytes) * steps_per_launch
     rec = {"MLUPS": round(mlups, 1), "nodes": spec.nodes, "steps": nsteps,
            "launch": f"{bx}x{by}g{groups}{'svt'[form]}",
-           "kernel": f"k_step{'2' if form == 2 else ''}<D2Q5{'' if nsets == 3 else 'V'},F32,emit>",
+           "kernel": f"{kname}<D2Q5{'' if nsets == 3 else 'V'},F32,emit>",
            "avg_launch_ms": round(avg_ms, 5), "bytes_per_launch": alg_bytes,
            "roofline_frac": round(alg_bytes / (avg_ms / 1e3) / 1e9 / HBM_PEAK_GBS, 4),
            "hbm_physical_frac": round(spec.nodes * (state_bytes + steps_per_launch * field_bytes)
@@ -1237,7 +1246,7 @@ def main():
     ap.add_argument("--sets", default="all", choices=["all", "velocity"],
                     help="distribution sets stored: all d+1 (the configuration) or the d velocity sets (Remark IV)")
     ap.add_argument("--launch", default="128x2g8t",
-                    help="cavity legs: threads per block, XCD groups and kernel form, BXxBYgG[s|v|t] (s: one node/thread, v: vector, t: two steps per launch)")
+                    help="cavity legs: threads per block, XCD groups and kernel form, BXxBYgG[s|v|t] (s: one node/thread, v: vector, t: several steps per launch)")
     ap.add_argument("--variants-study", metavar="OUT_JSONL",
                     help="velocity sets / Scheme II / force field against the plain update")
     ap.add_argument("--sweep", metavar="OUT_JSONL",
@@ -1251,8 +1260,8 @@ def main():
                     help="calibrated HBM traffic of the step kernel from rocprofv3 counter databases")
     ap.add_argument("--command", default="", help="command recorded in a summary")
     ap.add_argument("--traffic-kernel", default="batch2", choices=["batch2", "step2z", "step2"],
-                    help="kernel whose counters --summarize-traffic reads: the headline's batched two-step "
-                         "kernel, the 3D two-step kernel, or the 1024^2 cavity's two-step kernel")
+                    help="kernel whose counters --summarize-traffic reads: the headline's batched tile "
+                         "kernel, the 3D two-step kernel, or the 1024^2 cavity's tile kernel")
     ap.add_argument("--tgv3d", nargs="+", metavar="STORAGE FORM [GROUPS [BX BY]]",
                     help="time the 3D Taylor-Green step kernel (256^3) in one storage and form (XCD groups, "
                          "default 8; block, default 64 x 4)")
@@ -1339,13 +1348,13 @@ def main():
     if args.summarize_traffic:
         fdb, wdb, cfdb, cwdb, out_md = args.summarize_traffic
         if args.traffic_kernel == "batch2":
-            # the headline's dominant kernel: two-step batched launches of the
+            # the headline's dominant kernel: four-step batched launches of the
             # 512-case FP64 batch (no emission, no masks, non-temporal stores,
             # 32-bit node offsets); per-step algorithmic bytes of both steps
             from paper_2108_08591_amd import cases as C
             nodes = sum(b.spec.nodes for b in C.batch_cases(n=512))
-            md, ent = summarize_traffic(fdb, wdb, cfdb, cwdb, "k_step2_batch<LatD2Q5, 0, false, false, true, false>",
-                                        nodes * 2 * (2 * 15 * 8), "k_step2_batch<D2Q5,F64>_c4_512",
+            md, ent = summarize_traffic(fdb, wdb, cfdb, cwdb, "k_tile_batch<LatD2Q5, 0, true, 4, false, false, false>",
+                                        nodes * 4 * (2 * 15 * 8), "k_tile_batch<D2Q5,F64>_c4_512",
                                         args.command.split(" ;; "))
         elif args.traffic_kernel == "step2z":
             # the 3D Taylor-Green kernel at 256^3, two steps per launch, FP32
@@ -1355,8 +1364,8 @@ def main():
                                         args.command.split(" ;; "))
         else:
             nodes = 1024 * 1024
-            md, ent = summarize_traffic(fdb, wdb, cfdb, cwdb, "k_step2<LatD2Q5, 1, true, false, false, true>",
-                                        nodes * (2 * 15 * 4 + 2 * 4 * 4), "k_step2<D2Q5,F32,emit>_cavity1024",
+            md, ent = summarize_traffic(fdb, wdb, cfdb, cwdb, "k_tile<LatD2Q5, 1, true, 4, false, true, false>",
+                                        nodes * (2 * 15 * 4 + 4 * 4), "k_tile<D2Q5,F32,emit>_cavity1024",
                                         args.command.split(" ;; "))
         with open(out_md, "w") as fh:
             fh.write(md)

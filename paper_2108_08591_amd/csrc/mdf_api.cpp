@@ -379,10 +379,10 @@ std::vector<int> march_split(int64_t nsteps, int most)
     return plan;
 }
 
-// Advance case k by nsteps.  With the two-step form, pairs of steps run as
-// one launch and the call always ends with at least one one-step launch, so
-// that the buffer the read kernels pull from holds f*(t - 1) again; the
-// check (if any) rides on the last step.
+// Advance case k by nsteps, several steps (2D) or two (3D) per launch in form
+// 2.  The call always ends with at least one one-step launch, so that the
+// buffer the read kernels pull from holds f*(t - 1) again; the check (if any)
+// rides on the last step.
 mdf_status advance_case(mdf_ctx *ctx, int k, int64_t nsteps, bool check_last, uint32_t fields, void *out,
                         hipStream_t st, int *nblocks)
 {
@@ -546,11 +546,11 @@ mdf::BatchLaunch batch_args(mdf_ctx *ctx, uint32_t fields, int grid)
 }
 
 // nsteps batched steps of the uploaded active cases; the last one fused with
-// the check when `check`.  With the two-step form (2D axis-link lattices), pairs of steps run
-// as one launch of k_step2_batch and the chunk ends with at least one
-// one-step launch (which carries the check and leaves f*(t - 1) in the other
-// buffer for the read kernels).  A chunk whose length, form, check flag,
-// emission and starting parity were seen before replays a captured graph.
+// the check when `check`.  In form 2 (2D axis-link lattices) the chunk runs as
+// march_split() says and ends with at least one one-step launch (which carries
+// the check and leaves f*(t - 1) in the other buffer for the read kernels).  A
+// chunk whose length, form, check flag, emission and starting parity were seen
+// before replays a captured graph.
 mdf_status batch_steps(mdf_ctx *ctx, int nsteps, bool check, uint32_t fields, hipStream_t st)
 {
     if (nsteps <= 0) return MDF_OK;

@@ -1635,7 +1635,8 @@ __device__ __forceinline__ void step2z_plane2(const KCase &p, typename Store<ST>
 // links.  Every population, field and emitted value is bitwise that of two
 // one-step launches; the state crosses HBM once per two steps, plus the
 // halo ring ((TX + TY) 2 / (TX TY) of a read) and the two chunk-end planes
-// (2 / zc of a read).  Like k_step2, f*(t+1) never reaches HBM.
+// (2 / zc of a read).  f*(t+1) never reaches HBM: the buffer the
+// read kernels pull from is stale until the next one-step launch.
 template <class L, int ST, bool EMIT, bool MASK, bool NTST = false, bool WIDE = true>
 __global__ void __launch_bounds__(Fuse2Z<ST>::TX * Fuse2Z<ST>::TY, Fuse2Z<ST>::MINW)
 k_step2z(KCase p, Tiling tl, const typename Store<ST>::T *__restrict__ src, typename Store<ST>::T *__restrict__ dst,
