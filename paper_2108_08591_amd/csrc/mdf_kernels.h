@@ -2063,7 +2063,7 @@ hipError_t march_dispatch(const KCase &p, const CaseBufs &b, int src, int steps,
         } else {
 #define MDF_TILE_LAUNCH(K, G, E, M, LARGE)                                                                     \
     hipLaunchKernelGGL((k_tile<L, ST, LARGE, K, G, E, M>), dim3(tl.nb),                                        \
-                       dim3(TileShape<ST, LARGE>::W * TileShape<ST, LARGE>::H), 0, stream, p, tl, in, o, b.links, bits, emit)
+                       dim3(TileShape<ST, LARGE>::NT), 0, stream, p, tl, in, o, b.links, bits, emit)
             if (cover == kCoverSmall) MDF_SEVERAL_PICK(MDF_TILE_LAUNCH, 4, steps, gen, mask, emit_on, false);
             else MDF_SEVERAL_PICK(MDF_TILE_LAUNCH, 4, steps, gen, mask, emit_on, true);
 #undef MDF_TILE_LAUNCH
@@ -2171,7 +2171,7 @@ hipError_t march_batch_dispatch(const BatchLaunch &bl, bool emit, hipStream_t st
         } else {
 #define MDF_TILE_LAUNCH(K, G, E, M, LARGE)                                                                     \
     hipLaunchKernelGGL((k_tile_batch<L, ST, LARGE, K, G, E, M>), dim3(bl.grid),                                \
-                       dim3(TileShape<ST, LARGE>::W * TileShape<ST, LARGE>::H), 0, stream, bl.tab, bl.meta,    \
+                       dim3(TileShape<ST, LARGE>::NT), 0, stream, bl.tab, bl.meta,    \
                        bl.tile_start2, bl.active, bl.parity, bl.fields, bl.shape.groups)
             if (bl.cover == kCoverSmall) MDF_SEVERAL_PICK(MDF_TILE_LAUNCH, 4, steps, bl.gen, bl.mask, emit, false);
             else MDF_SEVERAL_PICK(MDF_TILE_LAUNCH, 4, steps, bl.gen, bl.mask, emit, true);

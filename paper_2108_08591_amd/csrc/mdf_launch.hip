@@ -118,13 +118,13 @@ int read_blocks(const KCase &p, LaunchShape s)
 
 // Strips for FP32 and the 16-bit formats beyond the Infinity Cache, where
 // the traffic per step counts (4096^2: FP32 116 us per step in strips and 166
-// in tiles, FP16 99 and 125); tiles inside it (1024^2: FP32 9.8 and 8.1 us,
-// FP16 13.9 and 9.4) and for FP64 (4096^2 320 and 310 us, 1024^2 21.5 and
-// 16.8), small ones up to 49152 nodes (128^2: FP64 1.3 us per step in small and
-// 1.6 in large ones, FP32 1.2 and 1.6; 256^2: 2.5 and 2.4, 1.7 and 1.8).
+// in tiles, FP16 99 and 125); tiles inside it (1024^2: FP32 9.8 and 7.5 us,
+// FP16 13.9 and 9.4) and for FP64 (4096^2 320 and 247 us, 1024^2 21.5 and
+// 13.4), small ones up to 73728 nodes (256^2: FP64 2.5 us per step in small and
+// 2.6 in large ones, FP32 1.7 and 1.9; 384^2: 4.0 and 3.1, 2.8 and 2.0).
 Cover march_cover(long long nodes, int storage, bool beyond_cache)
 {
-    if (nodes <= 49152) return kCoverSmall;
+    if (nodes <= 73728) return kCoverSmall;
     return storage != MDF_F64 && beyond_cache ? kCoverStrips : kCoverLarge;
 }
 
@@ -145,10 +145,8 @@ MarchGrid march_plan(const KCase &p, int storage, Cover cover)
 {
     MarchGrid g;
     if (cover != kCoverStrips) {
-        const bool large = cover == kCoverLarge, f64 = storage == MDF_F64;
-        const int sx = large ? TileShape<MDF_F32, true>::SX : TileShape<MDF_F32, false>::SX;
-        const int sy = !large ? TileShape<MDF_F32, false>::SY
-                              : (f64 ? TileShape<MDF_F64, true>::SY : TileShape<MDF_F32, true>::SY);
+        const int sx = cover == kCoverLarge ? TileShape<MDF_F32, true>::SX : TileShape<MDF_F32, false>::SX;
+        const int sy = cover == kCoverLarge ? TileShape<MDF_F32, true>::SY : TileShape<MDF_F32, false>::SY;
         g.nx = (p.nx + sx - 1) / sx;
         g.ny = (p.ny + sy - 1) / sy;
         g.rows = g.step = g.halo = 0;

@@ -327,28 +327,31 @@ __device__ __forceinline__ void march_strip(const KCase &pc, const MarchGrid &g,
 // Several steps where strips do not pay: in FP64, whose rows between the
 // steps do not fit the registers, and on grids inside the Infinity Cache,
 // where a strip's rows, one after the other in one wavefront, leave the chip
-// waiting for them.  A block owns a tile and its halo of 4 nodes, one node per
-// thread, and takes all K <= 4 steps of it at once: populations along x pass
-// between neighbouring lanes (DPP), those along y through LDS, in two
-// buffers, so that one barrier per step is enough.  The halo is computed
-// again by the neighbouring tiles.
-// Tiles are 16 x 16 threads (8 x 8 nodes written) on grids of at most
-// 49152 nodes, where the latency of a step counts and not its arithmetic, and
-// 32 x 32 (24 x 24), in FP64 32 x 16 (24 x 8), beyond: FP64 1024^2 19.3 us per
-// step with 32 x 32, 16.8 with 32 x 16 and 21.4 with 16 x 16; FP32 1024^2 8.1,
-// 8.3 and 11.7 us; FP32 64^2 1.6, 1.2 and 1.1 us.  (One and two steps per
-// launch, as before: 64^2 4.2 us in FP32 and 3.3 us in FP64 per step, 1024^2
-// 12.8 and 21.1 us.)
+// waiting for them.  A block owns a tile and its halo of 4 nodes, one or two
+// nodes per thread, and takes all K <= 4 steps of it at once: populations along
+// x pass between neighbouring lanes (DPP), those along y through LDS (or within
+// the thread), in two buffers, so that one barrier per step is enough.  The
+// halo is computed again by the neighbouring tiles.
+// Tiles are 16 x 16 threads (8 x 8 nodes written) on small grids, where the
+// latency of a step counts and not its arithmetic, and 32 x 32 nodes (24 x 24
+// written) beyond.  There a thread takes two nodes of a column in FP64 and
+// FP32: as many wavefronts fit a CU, with half the LDS and two independent
+// chains each (FP64 1024^2 19.3 us per step with one node, 16.8 with tiles of
+// 32 x 16, 13.4 with two nodes; FP32 8.1 and 7.5).  The 16-bit formats, which
+// convert every value at every step, keep one (FP16 1024^2 9.4 us, 9.9 with two).
+// One and two steps per launch, before: 64^2 4.2 us in FP32 and 3.3 us in FP64
+// per step (1.1 and 1.3 now), 1024^2 12.8 and 21.1 us.
 constexpr int kTileHalo = 4;
 template <int ST, bool LARGE>
 struct TileShape {
-    static constexpr int W = LARGE ? 32 : 16, H = !LARGE || ST == MDF_F64 ? 16 : 32;     // threads
-    static constexpr int SX = W - 2 * kTileHalo, SY = H - 2 * kTileHalo;                 // nodes written
+    static constexpr int W = LARGE ? 32 : 16, H = LARGE ? 32 : 16;             // columns and rows
+    static constexpr int R = LARGE && sizeof(typename Store<ST>::T) > 2 ? 2 : 1, NT = W * H / R;   // rows per thread, threads
+    static constexpr int SX = W - 2 * kTileHalo, SY = H - 2 * kTileHalo;       // nodes written
 };
 
 template <class L, int ST, bool LARGE>
 struct TileLds {
-    typename Store<ST>::C v[2][L::NS][2][TileShape<ST, LARGE>::W * TileShape<ST, LARGE>::H];
+    typename Store<ST>::C v[2][L::NS][2][TileShape<ST, LARGE>::NT];
 };
 
 template <class L, int ST, bool LARGE, int K, bool GEN, bool EMIT, bool MASK>
@@ -370,89 +373,111 @@ __device__ __forceinline__ void tile_steps(const KCase &pc, int gx, int tile,
         p.fmovef = 1.0f;
     }
     using TS = TileShape<ST, LARGE>;
-    constexpr int TW = TS::W, TH = TS::H, SX = TS::SX, SY = TS::SY;
-    const int e = threadIdx.x, tx = e % TW, ty = e / TW;
+    constexpr int R = TS::R;
+    const int e = threadIdx.x, tx = e % TS::W, ty = e / TS::W * R;
     const bool wallx = p.bc[0] == MDF_WALL, wally = p.bc[2] == MDF_WALL;
-    const int xu = (tile % gx) * SX - kTileHalo + tx, yu = (tile / gx) * SY - kTileHalo + ty;
-    int x = xu, y = yu;
+    const int xu = (tile % gx) * TS::SX - kTileHalo + tx, yu = (tile / gx) * TS::SY - kTileHalo + ty;
+    int x = xu;
     // wrapped on a periodic axis; clamped between walls (values beyond them are never used)
     if (wallx) x = x < 0 ? 0 : (x < p.nx ? x : p.nx - 1);
     else { x %= p.nx; x = x < 0 ? x + p.nx : x; }
-    if (wally) y = y < 0 ? 0 : (y < p.ny ? y : p.ny - 1);
-    else { y %= p.ny; y = y < 0 ? y + p.ny : y; }
-    const bool mine = unsigned(tx - kTileHalo) < unsigned(SX) && unsigned(ty - kTileHalo) < unsigned(SY) &&
-                      xu < p.nx && yu < p.ny;
-    const Ix32 own = grid_ix<false>(x, y, 0, p.ny, p.pitch);
-    const long long nodes = (long long)p.nx * p.ny;
-    unsigned lb = 0;
-    if (MASK && (!GEN || links)) lb = *elem(links, own);
-    Node<L, C> n;
-    load_sources<L, C>(p, (long long)y * p.nx + x, n);
-    C o[L::NS][L::Q];
-#pragma unroll
-    for (int a = 0; a < L::NS; ++a)
-#pragma unroll
-        for (int i = 0; i < L::Q; ++i)
-            o[a][i] = S::load(src + plane_of<L>(a, i) * p.dstride, own, rest_value<L, C>(p, a, i), p.scale);
+    const bool minex = unsigned(tx - kTileHalo) < unsigned(TS::SX) && xu < p.nx;
     const bool at_x0 = wallx && xu == 0, at_x1 = wallx && xu == p.nx - 1;
-    const bool at_y0 = wally && yu == 0, at_y1 = wally && yu == p.ny - 1;
-    const bool special = __builtin_amdgcn_ballot_w64(at_x0 || at_x1 || at_y0 || at_y1 || (lb & 0x7fu)) != 0;
-    const int below = ty > 0 ? e - TW : e, above = ty < TH - 1 ? e + TW : e;
+    const long long nodes = (long long)p.nx * p.ny;
+    int y[R];
+    unsigned lb[R];
+    bool mine[R], at_y0[R], at_y1[R];
+    Node<L, C> n[R];
+    C o[R][L::NS][L::Q];
+    bool wall = at_x0 || at_x1;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        y[r] = yu + r;
+        if (wally) y[r] = y[r] < 0 ? 0 : (y[r] < p.ny ? y[r] : p.ny - 1);
+        else { y[r] %= p.ny; y[r] = y[r] < 0 ? y[r] + p.ny : y[r]; }
+        mine[r] = minex && unsigned(ty + r - kTileHalo) < unsigned(TS::SY) && yu + r < p.ny;
+        at_y0[r] = wally && yu + r == 0;
+        at_y1[r] = wally && yu + r == p.ny - 1;
+        const Ix32 own = grid_ix<false>(x, y[r], 0, p.ny, p.pitch);
+        lb[r] = 0;
+        if (MASK && (!GEN || links)) lb[r] = *elem(links, own);
+        load_sources<L, C>(p, (long long)y[r] * p.nx + x, n[r]);
+#pragma unroll
+        for (int a = 0; a < L::NS; ++a)
+#pragma unroll
+            for (int i = 0; i < L::Q; ++i)
+                o[r][a][i] = S::load(src + plane_of<L>(a, i) * p.dstride, own, rest_value<L, C>(p, a, i), p.scale);
+        wall = wall || at_y0[r] || at_y1[r] || (lb[r] & 0x7fu);
+    }
+    const bool special = __builtin_amdgcn_ballot_w64(wall) != 0;
+    const int below = ty > 0 ? e - TS::W : e, above = ty < TS::H - R ? e + TS::W : e;
 #pragma unroll
     for (int j = 1; j <= K; ++j) {
+        auto &ex = lds.v[j & 1];
 #pragma unroll
         for (int a = 0; a < L::NS; ++a) {
-            lds.v[j & 1][a][0][e] = o[a][YP];
-            lds.v[j & 1][a][1][e] = o[a][YM];
+            ex[a][0][e] = o[R - 1][a][YP];
+            ex[a][1][e] = o[0][a][YM];
         }
         __syncthreads();
 #pragma unroll
-        for (int a = 0; a < L::NS; ++a) {
-            if (L::R == 1) n.f[a][0] = o[a][0];
-            n.f[a][XP] = lane_below(o[a][XP]);
-            n.f[a][XM] = lane_above(o[a][XM]);
-            n.f[a][YP] = lds.v[j & 1][a][0][below];
-            n.f[a][YM] = lds.v[j & 1][a][1][above];
-        }
+        for (int a = 0; a < L::NS; ++a)
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (L::R == 1) n[r].f[a][0] = o[r][a][0];
+                n[r].f[a][XP] = lane_below(o[r][a][XP]);
+                n[r].f[a][XM] = lane_above(o[r][a][XM]);
+                n[r].f[a][YP] = r > 0 ? o[r > 0 ? r - 1 : 0][a][YP] : ex[a][0][below];
+                n[r].f[a][YM] = r + 1 < R ? o[r + 1 < R ? r + 1 : r][a][YM] : ex[a][1][above];
+            }
         if (special) {
 #pragma unroll
-            for (int a = 0; a < L::NS; ++a) {
-                if (at_x0) n.f[a][XP] = bounced<L, C>(o[a][XM], a, XP, wall_of<L, C>(p, 0, a));
-                if (at_x1) n.f[a][XM] = bounced<L, C>(o[a][XP], a, XM, wall_of<L, C>(p, 1, a));
-                if (at_y0) n.f[a][YP] = bounced<L, C>(o[a][YM], a, YP, wall_of<L, C>(p, 2, a));
-                if (at_y1) n.f[a][YM] = bounced<L, C>(o[a][YP], a, YM, wall_of<L, C>(p, 3, a));
-                if (MASK) {
-                    if ((lb >> XP) & 1u) n.f[a][XP] = bounced<L, C>(o[a][XM], a, XP, C(0));
-                    if ((lb >> XM) & 1u) n.f[a][XM] = bounced<L, C>(o[a][XP], a, XM, C(0));
-                    if ((lb >> YP) & 1u) n.f[a][YP] = bounced<L, C>(o[a][YM], a, YP, C(0));
-                    if ((lb >> YM) & 1u) n.f[a][YM] = bounced<L, C>(o[a][YP], a, YM, C(0));
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int a = 0; a < L::NS; ++a) {
+                    if (at_x0) n[r].f[a][XP] = bounced<L, C>(o[r][a][XM], a, XP, wall_of<L, C>(p, 0, a));
+                    if (at_x1) n[r].f[a][XM] = bounced<L, C>(o[r][a][XP], a, XM, wall_of<L, C>(p, 1, a));
+                    if (at_y0[r]) n[r].f[a][YP] = bounced<L, C>(o[r][a][YM], a, YP, wall_of<L, C>(p, 2, a));
+                    if (at_y1[r]) n[r].f[a][YM] = bounced<L, C>(o[r][a][YP], a, YM, wall_of<L, C>(p, 3, a));
+                    if (MASK) {
+                        if ((lb[r] >> XP) & 1u) n[r].f[a][XP] = bounced<L, C>(o[r][a][XM], a, XP, C(0));
+                        if ((lb[r] >> XM) & 1u) n[r].f[a][XM] = bounced<L, C>(o[r][a][XP], a, XM, C(0));
+                        if ((lb[r] >> YP) & 1u) n[r].f[a][YP] = bounced<L, C>(o[r][a][YM], a, YP, C(0));
+                        if ((lb[r] >> YM) & 1u) n[r].f[a][YM] = bounced<L, C>(o[r][a][YP], a, YM, C(0));
+                    }
                 }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            Moments<L, C> m;
+            moments<L, C>(p, n[r], m);
+            if (EMIT && mine[r] && fields && (j == K || (fields & MDF_FIELD_ACCUMULATE))) {
+                const Ix32 node = grid_ix<false>(x, y[r], 0, p.ny, p.nx);
+                if (MASK && (lb[r] & 0x80u)) write_zero_fields<L, C>(fields, out, node, nodes);
+                else write_fields<L, C>(p, n[r], m, fields, out, node, nodes);
             }
-        }
-        Moments<L, C> m;
-        moments<L, C>(p, n, m);
-        if (EMIT && mine && fields && (j == K || (fields & MDF_FIELD_ACCUMULATE))) {
-            const Ix32 node = grid_ix<false>(x, y, 0, p.ny, p.nx);
-            if (MASK && (lb & 0x80u)) write_zero_fields<L, C>(fields, out, node, nodes);
-            else write_fields<L, C>(p, n, m, fields, out, node, nodes);
-        }
+            const Ix32 own = grid_ix<false>(x, y[r], 0, p.ny, p.pitch);
 #pragma unroll
-        for (int a = 0; a < L::NS; ++a) {
-            C fo[L::Q];
-            collide_fused<L, C>(p, n, m, a, fo, m.fb[a + L::A0]);
+            for (int a = 0; a < L::NS; ++a) {
+                C fo[L::Q];
+                collide_fused<L, C>(p, n[r], m, a, fo, m.fb[a + L::A0]);
 #pragma unroll
-            for (int i = 0; i < L::Q; ++i) {
-                const C rest = rest_value<L, C>(p, a, i);
-                if (j < K) o[a][i] = S::decode(S::encode(fo[i], rest, p.inv_scale), rest, p.scale);
-                else if (mine && !(MASK && (lb & 0x80u)))
-                    S::store(dst + plane_of<L>(a, i) * p.dstride, own, fo[i], rest, p.inv_scale);
+                for (int i = 0; i < L::Q; ++i) {
+                    const C rest = rest_value<L, C>(p, a, i);
+                    if (j < K) {
+                        o[r][a][i] = S::decode(S::encode(fo[i], rest, p.inv_scale), rest, p.scale);
+                        if (R > 1) asm volatile("" : "+v"(o[r][a][i]));       // (as in march_strip)
+                    } else if (mine[r] && !(MASK && (lb[r] & 0x80u))) {
+                        S::store(dst + plane_of<L>(a, i) * p.dstride, own, fo[i], rest, p.inv_scale);
+                    }
+                }
             }
         }
     }
 }
 
 template <class L, int ST, bool LARGE, int K, bool GEN, bool EMIT, bool MASK>
-__global__ void __launch_bounds__((TileShape<ST, LARGE>::W * TileShape<ST, LARGE>::H))
+__global__ void __launch_bounds__((TileShape<ST, LARGE>::NT))
 k_tile(KCase p, Tiling tl, const typename Store<ST>::T *__restrict__ src, typename Store<ST>::T *__restrict__ dst,
        const uint8_t *__restrict__ links, uint32_t fields, typename Store<ST>::C *__restrict__ out)
 {
@@ -476,7 +501,7 @@ k_march(KCase p, Tiling tl, MarchGrid g, const typename Store<ST>::T *__restrict
 // k_tile over the flat list of the tiles of a batch's active cases (prefix
 // offsets tile_start2, total meta[2]).
 template <class L, int ST, bool LARGE, int K, bool GEN, bool EMIT, bool MASK>
-__global__ void __launch_bounds__((TileShape<ST, LARGE>::W * TileShape<ST, LARGE>::H))
+__global__ void __launch_bounds__((TileShape<ST, LARGE>::NT))
 k_tile_batch(const BatchEntry *__restrict__ tab, const int *__restrict__ meta, const int *__restrict__ tile_start2,
              const int *__restrict__ active, int parity, uint32_t fields, int groups)
 {

@@ -62,8 +62,9 @@ def _compare(spec, storage, steps, mask=None, force=None, sets="all", label=""):
 
 
 # remainders of the tiles (8, 24 columns; 8, 24 rows) and sizes below them;
-# 224 x 219 and 300 x 170 lie on either side of the change of tile
-TILE_SIZES = [(1, 1), (2, 9), (8, 8), (9, 7), (24, 25), (33, 17), (64, 64), (224, 219), (300, 170)]
+# 288 x 256 and 289 x 257 lie on either side of the change of tile
+TILE_SIZES = [(1, 1), (2, 9), (8, 8), (9, 7), (24, 25), (33, 17), (64, 64), (224, 219), (300, 170), (288, 256),
+              (289, 257), (25, 3001), (3001, 25)]
 
 
 @pytest.mark.parametrize("storage", ["f64", "f32", "f16dev", "bf16dev"])
