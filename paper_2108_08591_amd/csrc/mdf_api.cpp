@@ -361,22 +361,16 @@ bool march_form(const mdf_ctx *ctx)
     return ctx->shape.fuse && lat_2d(ctx->lattice) && lat_fusable(ctx->lattice);
 }
 
-// Steps of each launch of a call of nsteps: launches of 3 .. most steps, as
-// even as they come, and one step at a time at the end, at least once, so
-// that the other buffer holds f*(t - 1) for the read kernels (and because
-// the check rides on a one-step launch).
-std::vector<int> march_split(int64_t nsteps, int most)
+// Steps of the next launch of a call that has `left` steps to go: 3 .. most, as
+// even as they come, and one at a time at the end, at least once, so that the
+// other buffer holds f*(t - 1) for the read kernels (and because the check
+// rides on a one-step launch).
+int march_next(int64_t left, int most)
 {
-    std::vector<int> plan;
-    int64_t m = nsteps - 1;
-    while (m >= 3) {
-        const int64_t launches = (m + most - 1) / most;
-        const int64_t n = std::max<int64_t>(3, (m + launches - 1) / launches);
-        plan.push_back(int(n));
-        m -= n;
-    }
-    plan.insert(plan.end(), size_t(m + 1), 1);
-    return plan;
+    const int64_t m = left - 1;
+    if (m < 3) return 1;
+    const int64_t launches = (m + most - 1) / most;
+    return int(std::max<int64_t>(3, (m + launches - 1) / launches));
 }
 
 // Advance case k by nsteps, several steps (2D) or two (3D) per launch in form
@@ -387,7 +381,8 @@ mdf_status advance_case(mdf_ctx *ctx, int k, int64_t nsteps, bool check_last, ui
                         hipStream_t st, int *nblocks)
 {
     if (march_form(ctx)) {
-        for (int n : march_split(nsteps, mdf::march_max(ctx->cover, ctx->storage))) {
+        while (nsteps > 0) {
+            const int n = march_next(nsteps, mdf::march_max(ctx->cover, ctx->storage));
             if (n == 1) {
                 nsteps -= 1;
                 mdf_status r = step_case(ctx, k, check_last && nsteps == 0, fields, out, st, nblocks);
@@ -547,7 +542,7 @@ mdf::BatchLaunch batch_args(mdf_ctx *ctx, uint32_t fields, int grid)
 
 // nsteps batched steps of the uploaded active cases; the last one fused with
 // the check when `check`.  In form 2 (2D axis-link lattices) the chunk runs as
-// march_split() says and ends with at least one one-step launch (which carries
+// march_next() says and ends with at least one one-step launch (which carries
 // the check and leaves f*(t - 1) in the other buffer for the read kernels).  A
 // chunk whose length, form, check flag, emission and starting parity were seen
 // before replays a captured graph.
@@ -558,25 +553,26 @@ mdf_status batch_steps(mdf_ctx *ctx, int nsteps, bool check, uint32_t fields, hi
     mdf_status r = batch_capacity_grid(ctx, &grid);
     if (r != MDF_OK) return r;
     const bool fuse = march_form(ctx);
-    std::vector<int> plan;                 // steps of each launch
-    if (fuse)
-        plan = march_split(nsteps, mdf::march_max(ctx->cover, ctx->storage));
-    else
-        plan.assign(nsteps, 1);
+    const int most = mdf::march_max(ctx->cover, ctx->storage);
+    auto next = [&](int left) { return fuse ? march_next(left, most) : 1; };
+    int launches = 0;
+    for (int left = nsteps; left > 0; left -= next(left)) ++launches;
     mdf::BatchLaunch bl = batch_args(ctx, fields, grid);
     mdf::BatchLaunch blm = batch_args(ctx, fields, ctx->batch_units);
     const int p0 = ctx->launches_since_upload & 1;
-    const int launches = int(plan.size());
     auto enqueue = [&]() -> hipError_t {
         hipError_t e = hipSuccess;
+        int left = nsteps;
         for (int l = 0; l < launches && e == hipSuccess; ++l) {
-            if (plan[l] > 1) {
+            const int n = next(left);
+            left -= n;
+            if (n > 1) {
                 blm.parity = (p0 + l) & 1;
-                blm.steps = plan[l];
+                blm.steps = n;
                 e = mdf::launch_march_batch(ctx->lattice, ctx->storage, blm, st);
             } else {
                 bl.parity = (p0 + l) & 1;
-                e = mdf::launch_step_batch(ctx->lattice, ctx->storage, bl, check && l == launches - 1, st);
+                e = mdf::launch_step_batch(ctx->lattice, ctx->storage, bl, check && left == 0, st);
             }
         }
         return e;
