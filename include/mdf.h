@@ -287,8 +287,8 @@ mdf_status mdf_invariants(const mdf_ctx *ctx, int32_t case_id, double *out, void
  *      with these bx, by; batched 3D contexts run every step as form 0.
  * The read kernels always use one node per thread.  Default 64 x 4, 8
  * groups, form 2 on the axis-link lattices (in 3D with FP64 and FP32
- * storage, on grids of a million nodes (FP64: 800 000) or more that the tiles cover with at
- * most 15 % of padding) and form 0 elsewhere; 3D axis-link lattices with 16-bit
+ * storage, on grids that fill its launch well: from about a million nodes,
+ * fewer without walls) and form 0 elsewhere; 3D axis-link lattices with 16-bit
  * storage default to 128 x 2 (64 x 4 where its rows waste less), one group,
  * form 0.
  * MDF_EINVAL otherwise (also forms 1 and 2 on D2Q9 / D3Q15).  Any shape

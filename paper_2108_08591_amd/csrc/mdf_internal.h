@@ -202,4 +202,45 @@ double lattice_cs2(int lattice);
 int grid_blocks(const KCase &p, int storage, LaunchShape shape);
 int read_blocks(const KCase &p, LaunchShape shape);
 
+// The 3D two-step launch: tiles of TX x TY nodes of a plane that walk chunks
+// of zc planes, and its fill, nodes advanced over node slots of its duration.
+constexpr int step2z_tx(int storage) { return storage == MDF_F32 || storage == MDF_F64 ? 32 : 64; }
+constexpr int step2z_ty(int storage) { return storage == MDF_F64 ? 4 : 8; }
+struct Step2zPlan {
+    int zc;
+    double fill;
+};
+
+// At most 32 planes per block (the two chunk-end planes then cost 2/32 of a
+// read).  Blocks stay resident for their whole chunk, so a launch takes as
+// long as its rounds of resident blocks times the zc + 2 planes that each
+// walks: the length with the least product is taken, the longest of several.
+// Resident are 256 CUs x as many copies of the LDS planes as 160 KB hold, two
+// for four sets of seven directions and three for three; of the 16-bit
+// formats, whose blocks are twice as large, two at their register budget.
+// Against lengths of 32, halved until 512 blocks were reached (per step):
+// 200 x 200 x 40 FP64 227 to 131 us, 138 x 148 x 60 123 to 100, FP32 cavity
+// 237 x 199 x 49 127 to 95; three sets 123 x 254 x 35 FP64 99 to 53, 192^3 FP32
+// 210 to 158; unchanged where the old length already filled its rounds (256^3
+// FP32 525).
+inline Step2zPlan step2z_plan(int storage, int sets, int q, int nx, int ny, int nz)
+{
+    const int tx = step2z_tx(storage), ty = step2z_ty(storage), ni = tx * ty;
+    const int bytes = storage == MDF_F64 ? 8 : storage == MDF_F32 ? 4 : 2;
+    const int lds = bytes * sets * (2 * ((q - 2) * ni + 2 * (tx + ty)) + 3 * 2 * ni);
+    const long long resident = 256ll * (bytes == 2 ? 2 : 163840 / lds);
+    const long long tiles = (long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty);
+    int zc = 0;
+    long long least = 0;
+    for (int most = nz < 32 ? nz : 32; most >= 1 && (zc == 0 || most >= 4); --most) {
+        const int chunks = (nz + most - 1) / most, len = (nz + chunks - 1) / chunks;
+        const long long cost = (tiles * chunks + resident - 1) / resident * (len + 2);
+        if (zc == 0 || cost < least) {
+            zc = len;
+            least = cost;
+        }
+    }
+    return {zc, double(nx) * ny * nz / (double(least) * resident * ni)};
+}
+
 }  // namespace mdf

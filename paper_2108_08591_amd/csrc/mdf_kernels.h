@@ -1361,9 +1361,9 @@ k_step(KCase p, Tiling tl, const typename Store<ST>::T *__restrict__ src, typena
 // faster than the 64 x 4 tile at the same budget, itself 5 % and 8 % faster
 // than at the compiler's.  FP32 and FP64 are bound to two 4-wave blocks per
 // CU by their LDS and keep the compiler's budget.
-template <int ST> struct Fuse2Z { static constexpr int TX = 64, TY = 8, MINW = 4; };
-template <> struct Fuse2Z<MDF_F32> { static constexpr int TX = 32, TY = 8, MINW = 1; };
-template <> struct Fuse2Z<MDF_F64> { static constexpr int TX = 32, TY = 4, MINW = 1; };
+template <int ST> struct Fuse2Z {
+    static constexpr int TX = step2z_tx(ST), TY = step2z_ty(ST), MINW = ST == MDF_F32 || ST == MDF_F64 ? 1 : 4;
+};
 
 // The directions of an axis-link 3D lattice by their z-component: the
 // in-plane ones (c_z = 0) in lattice order, and the +z and -z links.
@@ -1955,19 +1955,6 @@ hipError_t step_dispatch(const KCase &p, const CaseBufs &b, int src, bool check,
     return hipGetLastError();
 }
 
-// z-planes per block of k_step2z: 32 where the grid gives enough blocks
-// (the two chunk-end planes then cost 2/32 of a read), halved, down to 8,
-// while a launch would have fewer than 512 blocks, the two per CU that every
-// storage's LDS copy allows, so that small grids still fill the chip (at
-// 128^3, chunks of 32 planes left 128 blocks of the 16-bit tile and 256 of
-// the FP32 one).
-inline int step2z_chunk(int nz, int tiles_xy)
-{
-    int zc = nz < 32 ? nz : 32;
-    while (zc > 8 && (long long)tiles_xy * ((nz + zc - 1) / zc) < 512) zc /= 2;
-    return zc;
-}
-
 template <class L, int ST>
 hipError_t step2_dispatch(const KCase &p, const CaseBufs &b, int src, uint32_t fields, void *out, LaunchShape s,
                           hipStream_t stream)
@@ -1985,7 +1972,8 @@ hipError_t step2_dispatch(const KCase &p, const CaseBufs &b, int src, uint32_t f
         Tiling tl;
         tl.gx = (p.nx + TX - 1) / TX;
         tl.gy = (p.ny + TY - 1) / TY;
-        tl.zc = step2z_chunk(p.nz, tl.gx * tl.gy);
+        static_assert(2 * sizeof(Step2ZLds<L, ST>) <= 163840, "two blocks per CU");
+        tl.zc = step2z_plan(ST, L::NS, L::Q, p.nx, p.ny, p.nz).zc;
         tl.nb = tl.gx * tl.gy * ((p.nz + tl.zc - 1) / tl.zc);
         tl.groups = s.groups > 1 ? s.groups : 1;
         const bool emit_on = (fields != 0) && out != nullptr;
