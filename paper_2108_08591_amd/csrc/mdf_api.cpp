@@ -367,6 +367,9 @@ bool march_form(const mdf_ctx *ctx)
     return ctx->shape.fuse && lat_2d(ctx->lattice) && lat_fusable(ctx->lattice);
 }
 
+// Cases that take the kernels with a force field and Scheme II.
+bool general_case(const KCase &p) { return p.ffield != nullptr || p.forcing != MDF_FORCING_PLAIN; }
+
 // Steps of the next launch of a call that has `left` steps to go: 3 .. most, as
 // even as they come, and one at a time at the end, at least once, so that the
 // other buffer holds f*(t - 1) for the read kernels (and because the check
@@ -388,14 +391,16 @@ mdf_status advance_case(mdf_ctx *ctx, int k, int64_t nsteps, bool check_last, ui
 {
     if (march_form(ctx)) {
         while (nsteps > 0) {
-            const int n = march_next(nsteps, mdf::march_max(ctx->cover, ctx->storage));
+            const KCase &p = ctx->kc[k];
+            const int n = march_next(nsteps, mdf::march_max(ctx->cover, ctx->storage, ctx->bufs[k].links != nullptr,
+                                                            general_case(p)));
             if (n == 1) {
                 nsteps -= 1;
                 mdf_status r = step_case(ctx, k, check_last && nsteps == 0, fields, out, st, nblocks);
                 if (r != MDF_OK) return r;
                 continue;
             }
-            hipError_t e = mdf::launch_march(ctx->lattice, ctx->storage, ctx->kc[k], ctx->bufs[k], ctx->cur[k], n,
+            hipError_t e = mdf::launch_march(ctx->lattice, ctx->storage, p, ctx->bufs[k], ctx->cur[k], n,
                                              ctx->cover, fields, out, ctx->shape, st);
             if (e != hipSuccess) return device_error(ctx, e, "launch of several steps");
             ctx->cur[k] ^= 1;
@@ -539,7 +544,7 @@ mdf::BatchLaunch batch_args(mdf_ctx *ctx, uint32_t fields, int grid)
     bl.steps = 1;
     bl.cover = ctx->cover;
     bl.gen = false;
-    for (const KCase &p : ctx->kc) bl.gen = bl.gen || p.ffield || p.forcing != MDF_FORCING_PLAIN;
+    for (const KCase &p : ctx->kc) bl.gen = bl.gen || general_case(p);
     bl.mask = ctx->any_mask;
     bl.ntstore = ctx->kc[0].ntstore != 0;   // the same for every case of a context
     bl.shape = ctx->shape;
@@ -559,12 +564,12 @@ mdf_status batch_steps(mdf_ctx *ctx, int nsteps, bool check, uint32_t fields, hi
     mdf_status r = batch_capacity_grid(ctx, &grid);
     if (r != MDF_OK) return r;
     const bool fuse = march_form(ctx);
-    const int most = mdf::march_max(ctx->cover, ctx->storage);
+    mdf::BatchLaunch bl = batch_args(ctx, fields, grid);
+    mdf::BatchLaunch blm = batch_args(ctx, fields, ctx->batch_units);
+    const int most = mdf::march_max(ctx->cover, ctx->storage, blm.mask, blm.gen);
     auto next = [&](int left) { return fuse ? march_next(left, most) : 1; };
     int launches = 0;
     for (int left = nsteps; left > 0; left -= next(left)) ++launches;
-    mdf::BatchLaunch bl = batch_args(ctx, fields, grid);
-    mdf::BatchLaunch blm = batch_args(ctx, fields, ctx->batch_units);
     const int p0 = ctx->launches_since_upload & 1;
     auto enqueue = [&]() -> hipError_t {
         hipError_t e = hipSuccess;

@@ -186,10 +186,8 @@ hipError_t batch_blocks_per_cu(int lattice, int storage, LaunchShape shape, bool
 // Batched launch of bl.steps steps over the list of units (the 2D lattices with axis links).
 hipError_t launch_march_batch(int lattice, int storage, const BatchLaunch &bl, hipStream_t stream);
 // Units of launches of several steps of a context with `nodes` nodes in all
-// its cases, the most steps such a launch takes (at least 3), and the units
-// of one case.
+// its cases, and the units of one case.
 Cover march_cover(long long nodes, int storage, bool beyond_cache);
-int march_max(Cover cover, int storage);
 MarchGrid march_plan(const KCase &p, int storage, Cover cover);
 hipError_t launch_finalize_batch(const BatchEntry *tab, const int *meta, const int *active, int nactive,
                                  hipStream_t stream);
@@ -201,6 +199,18 @@ double lattice_cs2(int lattice);
 // Blocks of one step launch / one read launch.
 int grid_blocks(const KCase &p, int storage, LaunchShape shape);
 int read_blocks(const KCase &p, LaunchShape shape);
+
+// Most steps of a launch of several steps: four, and five in FP32 strips
+// without obstacles, force field and Scheme II (21 steps, five and four at a
+// time, and with five the registers that do not fit: 8192^2 plain 9.52 and
+// 11.42 ms, with emitted fields 12.15 and 13.64 ms, 8 registers).  With
+// obstacles 38 registers do not fit (20.9 and 11.4 ms; and emitted fields, 80,
+// 32.9 and 13.4 ms), with a force field or Scheme II 84 (39.3 and 16.0 ms, 31.9
+// and 11.6 ms).  Five steps of the 16-bit formats do not fit either.
+inline int march_max(Cover cover, int storage, bool mask, bool gen)
+{
+    return cover == kCoverStrips && storage == MDF_F32 && !mask && !gen ? 5 : 4;
+}
 
 // The 3D two-step launch: tiles of TX x TY nodes of a plane that walk chunks
 // of zc planes, and its fill, nodes advanced over node slots of its duration.

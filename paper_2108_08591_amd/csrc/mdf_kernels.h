@@ -1994,14 +1994,16 @@ hipError_t step2_dispatch(const KCase &p, const CaseBufs &b, int src, uint32_t f
     }
 }
 
-// M(K, GEN, EMIT, MASK, ...) for the kernel of a launch of `steps` steps, up to
-// KMAX.  Force fields and Scheme II take one kernel, which also covers masks
-// and emission.
+// M(K, GEN, EMIT, MASK, ...) for the kernel of a launch of `steps` steps (up to
+// KMAX; five only without force field, Scheme II and mask, as march_max() has
+// it).  Force fields and Scheme II take one kernel, which also covers masks and
+// emission.
 #define MDF_SEVERAL_PICK(M, KMAX, steps, gen, mask, emit, ...)                                     \
     do {                                                                                           \
         if (steps == 3) MDF_SEVERAL_PICK1(M, 3, gen, mask, emit, __VA_ARGS__);                     \
         else if (steps == 4) MDF_SEVERAL_PICK1(M, 4, gen, mask, emit, __VA_ARGS__);                \
-        else if (KMAX > 4 && steps == KMAX) MDF_SEVERAL_PICK1(M, KMAX, gen, mask, emit, __VA_ARGS__); \
+        else if (KMAX > 4 && steps == KMAX && !(gen) && !(mask) && (emit)) M(KMAX, false, true, false, __VA_ARGS__); \
+        else if (KMAX > 4 && steps == KMAX && !(gen) && !(mask)) M(KMAX, false, false, false, __VA_ARGS__); \
         else return hipErrorInvalidValue;                                                          \
     } while (0)
 #define MDF_SEVERAL_PICK1(M, K, gen, mask, emit, ...)                                              \

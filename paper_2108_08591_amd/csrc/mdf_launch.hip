@@ -128,10 +128,6 @@ Cover march_cover(long long nodes, int storage, bool beyond_cache)
     return storage != MDF_F64 && beyond_cache ? kCoverStrips : kCoverLarge;
 }
 
-// Four steps, in FP32 strips five (8192^2, 20 steps and a read-out: 10.4 ms
-// against 12.3 ms with four; five of the 16-bit formats spill registers).
-int march_max(Cover cover, int storage) { return cover == kCoverStrips && storage == MDF_F32 ? 5 : 4; }
-
 // Strips have one column of halo per step on either side, or, in FP32, 8:
 // 48 columns written, whose rows start and end on 64-byte blocks, so that no
 // two strips write into the same block (8192^2, five steps: 2.17 ms per pass
@@ -153,7 +149,7 @@ MarchGrid march_plan(const KCase &p, int storage, Cover cover)
         return g;
     }
     const bool wallx = p.bc[0] == MDF_WALL;
-    g.halo = storage == MDF_F32 ? 8 : march_max(cover, storage);
+    g.halo = storage == MDF_F32 ? 8 : 4;
     g.step = 64 - 2 * g.halo;
     g.nx = 1;
     if (wallx ? p.nx <= 64 : (p.nx <= 64 && 64 % p.nx == 0)) g.halo = 0;

@@ -1,0 +1,22 @@
+// launch_rules.cpp -- prints what the launch rules of mdf_internal.h choose, for
+// the questions on standard input, one a line.  Built and driven by
+// tests/test_launch_rules_cpu.py; no call reaches the device.
+#include <cstdio>
+#include <cstring>
+
+#include "mdf_internal.h"
+
+int main()
+{
+    char what[32];
+    while (std::scanf("%31s", what) == 1) {
+        int a[8] = {};
+        if (!std::strcmp(what, "most")) {               // cover storage mask gen
+            if (std::scanf("%d%d%d%d", a, a + 1, a + 2, a + 3) != 4) return 1;
+            std::printf("%d\n", mdf::march_max(mdf::Cover(a[0]), a[1], a[2] != 0, a[3] != 0));
+        } else {
+            return 1;
+        }
+    }
+    return 0;
+}
