@@ -1,0 +1,74 @@
+"""The kernels of launches of several steps in 2D that a call picks by its
+options, bitwise against one-step launches (which are checked against the
+oracle elsewhere)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2108_08591_amd import mdf
+from test_gpu_several_steps import _spec
+
+pytestmark = pytest.mark.gpu
+
+MOM = mdf.FIELD_MOMENTS
+# a remainder of the tiles, small and large, and strips (FP32 and 16-bit beyond
+# the Infinity Cache)
+GRIDS = [("f64", 70, 45), ("f64", 300, 259), ("f32", 300, 259), ("f32", 1500, 1520), ("f16dev", 300, 259),
+         ("f16dev", 2100, 2201), ("bf16dev", 2100, 2201)]
+
+
+def _init(nx, ny, storage, seed=0):
+    g = torch.Generator().manual_seed(seed + nx)
+    data = (torch.rand(3, ny, nx, generator=g, dtype=torch.float64) - 0.5) * 0.1
+    return data.to(torch.float64 if storage == "f64" else torch.float32)
+
+
+@pytest.mark.parametrize("storage,nx,ny", GRIDS)
+@pytest.mark.parametrize("scheme2", [False, True])
+@pytest.mark.parametrize("mask", [False, True])
+def test_forced_without_and_with_emission(storage, nx, ny, scheme2, mask):
+    """Force field and Scheme II, with a mask and without: steps alone (a kernel
+    of its own each), then steps that emit (one kernel for both)."""
+    print(f"[gpu] forced {storage} {nx}x{ny} scheme2={scheme2} mask={mask}", flush=True)
+    out = []
+    for form in (0, 2):
+        rng = np.random.default_rng(nx)
+        data = _init(nx, ny, storage)
+        solid = (rng.random((ny, nx)) < 0.05).astype(np.uint8) if mask else None
+        if mask:
+            data[:, torch.as_tensor(solid).bool()] = 0.0
+        s = mdf.Solver(_spec(nx, ny, True, False, rng, scheme2=scheme2), storage=storage,
+                       solid=[solid] if mask else None, init=("fields", [data]), u_ref=0.1)
+        s.set_launch(64, 4, 8, form)
+        if not scheme2:
+            s.set_force_field(torch.as_tensor(rng.uniform(-1e-4, 1e-4, (2, ny, nx))))
+        s.step(8)
+        got = [s.populations()]
+        s.step(4)
+        out.append(got + [s.populations()] + s.step_emit(9, MOM))
+    assert all(torch.isfinite(t).all() for t in out[0])
+    assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("storage,sizes", [("f64", [(70, 45), (33, 90)]), ("f32", [(1200, 1100), (64, 64)]),
+                                           ("f16dev", [(2100, 1600), (57, 300)])])
+def test_forced_batches(storage, sizes):
+    """A batch in which one case has a force field and no case a mask."""
+    print(f"[gpu] forced batch {storage} {sizes}", flush=True)
+    stream = torch.cuda.Stream()
+    out = []
+    for form in (0, 2):
+        rng = np.random.default_rng(7)
+        specs = [_spec(nx, ny, True, k % 2 == 0, rng) for k, (nx, ny) in enumerate(sizes)]
+        init = [_init(nx, ny, storage, k) for k, (nx, ny) in enumerate(sizes)]
+        with torch.cuda.stream(stream):
+            s = mdf.Solver(specs, storage=storage, init=("fields", init), u_ref=0.1, stream=stream)
+            s.set_launch(64, 4, 8, form)
+            nx, ny = sizes[1]
+            s.set_force_field(torch.as_tensor(rng.uniform(-1e-4, 1e-4, (2, ny, nx))), case=1)
+            for _ in range(3):
+                s.step(8)
+            out.append([s.populations(k) for k in range(2)] + s.step_emit(9, MOM))
+        stream.synchronize()
+    assert all(torch.isfinite(t).all() for t in out[0])
+    assert all(torch.equal(a, b) for a, b in zip(*out))
