@@ -131,7 +131,7 @@ struct CaseLayout {
 
 // Context-wide regions of the workspace (batched launches).
 struct SharedLayout {
-    size_t table, meta, tile_start, tile_start2, active;
+    size_t table, meta, tile_start, tile_start2, tile_start3, active;
 };
 
 // Blocks of the largest grid any allowed launch shape produces
@@ -203,6 +203,8 @@ size_t layout(int lattice, int storage, const mdf_case *cases, int ncases, bool 
     off = align256(off + size_t(ncases + 1) * sizeof(int));
     sh.tile_start2 = off;
     off = align256(off + size_t(ncases + 1) * sizeof(int));
+    sh.tile_start3 = off;
+    off = align256(off + size_t(ncases + 1) * sizeof(int));
     sh.active = off;
     off = align256(off + size_t(ncases) * sizeof(int));
     if (shared) *shared = sh;
@@ -253,10 +255,11 @@ struct mdf_ctx {
     bool any_mask = false;
     mdf::Cover cover = mdf::kCoverSmall; // units of launches of several steps
     mdf::BatchEntry *d_tab = nullptr;
-    int *d_meta = nullptr, *d_tile_start = nullptr, *d_tile_start2 = nullptr, *d_active = nullptr;
+    int *d_meta = nullptr, *d_tile_start = nullptr, *d_tile_start2 = nullptr, *d_tile_start3 = nullptr,
+        *d_active = nullptr;
     double *d_results = nullptr;
     std::vector<mdf::BatchEntry> h_tab;
-    std::vector<int> h_tile_start, h_tile_start2, h_active, h_meta;
+    std::vector<int> h_tile_start, h_tile_start2, h_tile_start3, h_active, h_meta;
     std::vector<double> h_results;
     int launches_since_upload = 0;       // buffer parity of the uploaded table
     int uploaded_fields = -1;
@@ -361,7 +364,8 @@ mdf_status step_case(mdf_ctx *ctx, int k, bool check, uint32_t fields, void *out
     return MDF_OK;
 }
 
-// 2D axis-link lattices in form 2 run launches of several steps (k_tile, k_march).
+// 2D axis-link lattices in form 2 run launches of several steps (k_step2 of two,
+// k_tile and k_march of more).
 bool march_form(const mdf_ctx *ctx)
 {
     return ctx->shape.fuse && lat_2d(ctx->lattice) && lat_fusable(ctx->lattice);
@@ -369,18 +373,6 @@ bool march_form(const mdf_ctx *ctx)
 
 // Cases that take the kernels with a force field and Scheme II.
 bool general_case(const KCase &p) { return p.ffield != nullptr || p.forcing != MDF_FORCING_PLAIN; }
-
-// Steps of the next launch of a call that has `left` steps to go: 3 .. most, as
-// even as they come, and one at a time at the end, at least once, so that the
-// other buffer holds f*(t - 1) for the read kernels (and because the check
-// rides on a one-step launch).
-int march_next(int64_t left, int most)
-{
-    const int64_t m = left - 1;
-    if (m < 3) return 1;
-    const int64_t launches = (m + most - 1) / most;
-    return int(std::max<int64_t>(3, (m + launches - 1) / launches));
-}
 
 // Advance case k by nsteps, several steps (2D) or two (3D) per launch in form
 // 2.  The call always ends with at least one one-step launch, so that the
@@ -392,16 +384,18 @@ mdf_status advance_case(mdf_ctx *ctx, int k, int64_t nsteps, bool check_last, ui
     if (march_form(ctx)) {
         while (nsteps > 0) {
             const KCase &p = ctx->kc[k];
-            const int n = march_next(nsteps, mdf::march_max(ctx->cover, ctx->storage, ctx->bufs[k].links != nullptr,
-                                                            general_case(p)));
+            const int n = mdf::march_next(nsteps, mdf::march_max(ctx->cover, ctx->storage,
+                                                                 ctx->bufs[k].links != nullptr, general_case(p)));
             if (n == 1) {
                 nsteps -= 1;
                 mdf_status r = step_case(ctx, k, check_last && nsteps == 0, fields, out, st, nblocks);
                 if (r != MDF_OK) return r;
                 continue;
             }
-            hipError_t e = mdf::launch_march(ctx->lattice, ctx->storage, p, ctx->bufs[k], ctx->cur[k], n,
-                                             ctx->cover, fields, out, ctx->shape, st);
+            hipError_t e = n == 2 ? mdf::launch_step2(ctx->lattice, ctx->storage, p, ctx->bufs[k], ctx->cur[k], fields,
+                                                      out, ctx->shape, st)
+                                  : mdf::launch_march(ctx->lattice, ctx->storage, p, ctx->bufs[k], ctx->cur[k], n,
+                                                      ctx->cover, fields, out, ctx->shape, st);
             if (e != hipSuccess) return device_error(ctx, e, "launch of several steps");
             ctx->cur[k] ^= 1;
             ctx->time[k] += n;
@@ -484,6 +478,10 @@ mdf_status batch_upload(mdf_ctx *ctx, const std::vector<int> &active, uint32_t f
         e.gy = (e.p.ny + ctx->shape.by - 1) / ctx->shape.by;
         e.ntiles = e.gx * e.gy * e.p.nz;
         if (lat_2d(ctx->lattice) && lat_fusable(ctx->lattice)) {
+            const int rows = mdf::step2_rows(ctx->storage);
+            e.gx2 = (e.p.nx + 63) / 64;
+            e.gy2 = (e.p.ny + rows - 1) / rows;
+            e.ntiles2 = e.gx2 * e.gy2;
             e.march = mdf::march_plan(e.p, ctx->storage, ctx->cover);
             units += (long long)e.march.nx * e.march.ny;
         }
@@ -501,15 +499,19 @@ mdf_status batch_upload(mdf_ctx *ctx, const std::vector<int> &active, uint32_t f
     if (total > 0x7fffffffLL) return fail(ctx, MDF_EINVAL, "batch has too many tiles");
     ctx->h_tile_start[active.size()] = int(total);
     ctx->h_tile_start2.assign(active.size() + 1, 0);
-    long long total2 = 0;
+    ctx->h_tile_start3.assign(active.size() + 1, 0);
+    long long total2 = 0, total3 = 0;
     for (size_t i = 0; i < active.size(); ++i) {
+        ctx->h_tile_start3[i] = int(total3);
+        total3 += ctx->h_tab[active[i]].ntiles2;
         ctx->h_tile_start2[i] = int(total2);
         const mdf::MarchGrid &g = ctx->h_tab[active[i]].march;
         total2 += (long long)g.nx * g.ny;
     }
-    if (units > 0x7fffffffLL) return fail(ctx, MDF_EINVAL, "batch has too many tiles");
+    if (units > 0x7fffffffLL || total3 > 0x7fffffffLL) return fail(ctx, MDF_EINVAL, "batch has too many tiles");
     ctx->h_tile_start2[active.size()] = int(total2);
-    ctx->h_meta = {int(active.size()), int(total), int(total2), 0};
+    ctx->h_tile_start3[active.size()] = int(total3);
+    ctx->h_meta = {int(active.size()), int(total), int(total2), int(total3)};
     hipError_t e = hipMemcpyAsync(ctx->d_tab, ctx->h_tab.data(), sizeof(mdf::BatchEntry) * n, hipMemcpyHostToDevice, st);
     if (e == hipSuccess)
         e = hipMemcpyAsync(ctx->d_meta, ctx->h_meta.data(), sizeof(int) * 4, hipMemcpyHostToDevice, st);
@@ -518,6 +520,9 @@ mdf_status batch_upload(mdf_ctx *ctx, const std::vector<int> &active, uint32_t f
                            hipMemcpyHostToDevice, st);
         if (e == hipSuccess)
             e = hipMemcpyAsync(ctx->d_tile_start2, ctx->h_tile_start2.data(), sizeof(int) * (active.size() + 1),
+                               hipMemcpyHostToDevice, st);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(ctx->d_tile_start3, ctx->h_tile_start3.data(), sizeof(int) * (active.size() + 1),
                                hipMemcpyHostToDevice, st);
         if (e == hipSuccess)
             e = hipMemcpyAsync(ctx->d_active, active.data(), sizeof(int) * active.size(), hipMemcpyHostToDevice, st);
@@ -537,6 +542,7 @@ mdf::BatchLaunch batch_args(mdf_ctx *ctx, uint32_t fields, int grid)
     bl.meta = ctx->d_meta;
     bl.tile_start = ctx->d_tile_start;
     bl.tile_start2 = ctx->d_tile_start2;
+    bl.tile_start3 = ctx->d_tile_start3;
     bl.active = ctx->d_active;
     bl.parity = 0;
     bl.fields = fields;
@@ -567,9 +573,19 @@ mdf_status batch_steps(mdf_ctx *ctx, int nsteps, bool check, uint32_t fields, hi
     mdf::BatchLaunch bl = batch_args(ctx, fields, grid);
     mdf::BatchLaunch blm = batch_args(ctx, fields, ctx->batch_units);
     const int most = mdf::march_max(ctx->cover, ctx->storage, blm.mask, blm.gen);
-    auto next = [&](int left) { return fuse ? march_next(left, most) : 1; };
-    int launches = 0;
-    for (int left = nsteps; left > 0; left -= next(left)) ++launches;
+    auto next = [&](int left) { return fuse ? mdf::march_next(left, most) : 1; };
+    int launches = 0, grid2 = 0;
+    bool two = false;
+    for (int left = nsteps; left > 0; left -= next(left)) {
+        ++launches;
+        two = two || next(left) == 2;
+    }
+    if (two) {
+        int per_cu = 0;
+        hipError_t e = mdf::batch2_blocks_per_cu(ctx->lattice, ctx->storage, ctx->any_mask, &per_cu);
+        if (e != hipSuccess) return device_error(ctx, e, "occupancy query");
+        grid2 = ctx->num_cu * (per_cu < 1 ? 1 : per_cu);
+    }
     const int p0 = ctx->launches_since_upload & 1;
     auto enqueue = [&]() -> hipError_t {
         hipError_t e = hipSuccess;
@@ -577,7 +593,12 @@ mdf_status batch_steps(mdf_ctx *ctx, int nsteps, bool check, uint32_t fields, hi
         for (int l = 0; l < launches && e == hipSuccess; ++l) {
             const int n = next(left);
             left -= n;
-            if (n > 1) {
+            if (n == 2) {
+                mdf::BatchLaunch bl2 = bl;
+                bl2.parity = (p0 + l) & 1;
+                bl2.grid = grid2;
+                e = mdf::launch_step2_batch(ctx->lattice, ctx->storage, bl2, st);
+            } else if (n > 1) {
                 blm.parity = (p0 + l) & 1;
                 blm.steps = n;
                 e = mdf::launch_march_batch(ctx->lattice, ctx->storage, blm, st);
@@ -737,6 +758,7 @@ mdf_status mdf_init(mdf_ctx **out, mdf_lattice lattice, mdf_storage storage, con
     ctx->d_meta = reinterpret_cast<int *>(ws + shl.meta);
     ctx->d_tile_start = reinterpret_cast<int *>(ws + shl.tile_start);
     ctx->d_tile_start2 = reinterpret_cast<int *>(ws + shl.tile_start2);
+    ctx->d_tile_start3 = reinterpret_cast<int *>(ws + shl.tile_start3);
     ctx->d_active = reinterpret_cast<int *>(ws + shl.active);
     ctx->d_results = reinterpret_cast<double *>(ws + lay[0].result);
     ctx->h_results.assign(size_t(ncases) * mdf::kNRed, 0.0);

@@ -103,6 +103,7 @@ struct BatchEntry {
     double *result;
     void *out;              // emitted fields of the current call, or null
     int gx, gy, ntiles;     // tile grid of the case for the batch launch shape
+    int gx2, gy2, ntiles2;  // tile grid of two-step launches (2D axis-link lattices), else 0
     MarchGrid march;        // units of launches of several steps (2D axis-link lattices), else zero
     int cur;                // buffer holding f*(t) when the table was uploaded
 };
@@ -113,10 +114,11 @@ struct BatchLaunch {
     const int *meta;        // device: {active cases, total tiles}
     const int *tile_start;  // device: prefix offsets of the active cases' tiles
     const int *tile_start2; // device: the same for the units of launches of several steps
+    const int *tile_start3; // device: the same for two-step tiles
     const int *active;      // device: case ids of the active cases
     int parity;             // launches since the table upload, mod 2
     uint32_t fields;        // emitted fields (0: none)
-    int grid;               // blocks of the persistent launch (one step), units of all cases (several)
+    int grid;               // blocks of the persistent launch (one and two steps), units of all cases (more)
     int steps;              // steps of the launch
     Cover cover;            // units of several steps
     bool gen;               // any case has a force field or runs Scheme II
@@ -139,8 +141,10 @@ struct LatOps {
     hipError_t (*init)(int storage, const KCase &p, const CaseBufs &b, int cur, int kind, const void *data,
                        hipStream_t stream);
     hipError_t (*batch)(int storage, const BatchLaunch &bl, bool check, bool emit, hipStream_t stream);
+    hipError_t (*batch2)(int storage, const BatchLaunch &bl, bool emit, hipStream_t stream);
     hipError_t (*march_batch)(int storage, const BatchLaunch &bl, bool emit, hipStream_t stream);
     hipError_t (*batch_cap)(int storage, LaunchShape shape, bool mask, int *blocks_per_cu);
+    hipError_t (*batch2_cap)(int storage, bool mask, int *blocks_per_cu);
     hipError_t (*links)(const KCase &p, const uint8_t *solid, uint8_t *links, hipStream_t stream);
     double cs2;             // the lattice's c_s^2 (of the velocity sets, on a lattice per set)
 };
@@ -165,7 +169,7 @@ hipError_t launch_links(int lattice, const KCase &p, const uint8_t *solid, uint8
                         hipStream_t stream);
 hipError_t launch_init(int lattice, int storage, const KCase &p, const CaseBufs &b, int cur,
                        int kind, const void *data, hipStream_t stream);
-// Two steps in one launch (D3Q7, D3Q6 and their *_V forms): f*(t) in pop[src] -> f*(t+2) in
+// Two steps in one launch (the lattices with axis links): f*(t) in pop[src] -> f*(t+2) in
 // pop[src ^ 1]; fields (if any) emitted at both steps.
 hipError_t launch_step2(int lattice, int storage, const KCase &p, const CaseBufs &b, int src, uint32_t fields,
                         void *out, LaunchShape shape, hipStream_t stream);
@@ -183,6 +187,12 @@ hipError_t launch_read(int lattice, int storage, const KCase &p, const CaseBufs 
 hipError_t launch_finalize(const CaseBufs &b, int nblocks, hipStream_t stream);
 hipError_t launch_step_batch(int lattice, int storage, const BatchLaunch &bl, bool check, hipStream_t stream);
 hipError_t batch_blocks_per_cu(int lattice, int storage, LaunchShape shape, bool mask, int *blocks_per_cu);
+// Batched two steps per launch (the 2D lattices with axis links) over the
+// two-step tile list.
+hipError_t launch_step2_batch(int lattice, int storage, const BatchLaunch &bl, hipStream_t stream);
+hipError_t batch2_blocks_per_cu(int lattice, int storage, bool mask, int *blocks_per_cu);
+// Two-step tile grid of a 2D case: tiles of 64 x rows nodes.
+int step2_rows(int storage);
 // Batched launch of bl.steps steps over the list of units (the 2D lattices with axis links).
 hipError_t launch_march_batch(int lattice, int storage, const BatchLaunch &bl, hipStream_t stream);
 // Units of launches of several steps of a context with `nodes` nodes in all
@@ -210,6 +220,19 @@ int read_blocks(const KCase &p, LaunchShape shape);
 inline int march_max(Cover cover, int storage, bool mask, bool gen)
 {
     return cover == kCoverStrips && storage == MDF_F32 && !mask && !gen ? 5 : 4;
+}
+
+// Steps of the next launch of a call that has `left` steps to go: 2 .. most, as
+// even as they come, but for the last step, which is a launch of its own, so
+// that the other buffer holds f*(t - 1) for the read kernels (and because the
+// check rides on a one-step launch).  A call of three steps, two and one: 8192^2
+// FP32 2.97 ms, 4.27 in launches of one step, FP64 1024^2 78 and 110 us.
+inline int march_next(int64_t left, int most)
+{
+    const int64_t m = left - 1;
+    if (m < 2) return 1;
+    const int64_t launches = (m + most - 1) / most;
+    return int((m + launches - 1) / launches);
 }
 
 // The 3D two-step launch: tiles of TX x TY nodes of a plane that walk chunks

@@ -1343,6 +1343,249 @@ k_step(KCase p, Tiling tl, const typename Store<ST>::T *__restrict__ src, typena
                                                     snap, partial);
 }
 
+// ----------------------------------------------------------------- two steps per pass (2D, axis links)
+
+// Output rows of one tile of k_step2 per storage.  The LDS copy of the
+// intermediate state (NS * Q planes of (64 + 2) x (rows + 2) stored values)
+// is 47.5 KB for FP64, 39.6 KB for FP32 and 19.8 KB for the 16-bit formats
+// (D2Q5, three sets).  The 16-bit formats keep 8 rows rather than 16: their
+// step 1 then pulls the halo tile in one batch of three nodes per thread,
+// not two, and more blocks fit per CU (measured +19-25 % at 4096^2 and
+// 8192^2).
+template <int ST> struct Fuse2Rows { static constexpr int TY = 8, NT = 256; };
+template <> struct Fuse2Rows<MDF_F64> { static constexpr int TY = 4, NT = 256; };
+
+constexpr int kF2X = 64;                 // output columns of a tile
+constexpr int kF2W = kF2X + 2;           // columns of the tile plus its one-node halo
+constexpr int kF2Strip = 16;             // tiles per strip of the two-step tile walk
+
+// Two-step tile t of a gx x gy grid, walked in vertical strips kF2Strip
+// tiles wide (the last strip takes the remaining columns): the tiles of one
+// strip row are consecutive and the strip's rows follow each other, so a
+// tile's neighbours in y run shortly before and after it, in the same XCD
+// band, while the halo rows they share are still in that XCD's L2.  Row by
+// row over a wide grid, one row of tiles (8192 x 10 rows x 15 FP32 planes,
+// 4.9 MB) would exceed the L2 before the next row reused its halo.  A
+// bijection on [0, gx * gy); with gx <= kF2Strip it is the row-major order.
+__device__ __forceinline__ void strip_tile(int t, int gx, int gy, int &tx, int &ty)
+{
+    const int full = gx / kF2Strip;        // strips of full width
+    const int per = kF2Strip * gy;         // tiles in one full strip
+    const int s = t / per;
+    if (s < full) {
+        const int r = t - s * per;
+        ty = r / kF2Strip;
+        tx = s * kF2Strip + r % kF2Strip;
+    } else {
+        const int w = gx - full * kF2Strip;
+        const int r = t - full * per;
+        ty = r / w;
+        tx = full * kF2Strip + r % w;
+    }
+}
+
+// Two time steps in one pass over HBM (temporal blocking, 2D).  A block
+// owns a tile of 64 x TY nodes.  Step 1 runs on the tile and a one-node
+// halo with the one-step code (pull from the post-collision state f*(t) in
+// HBM, wall rule, moments, collision); its result f*(t+1) goes to LDS in the
+// storage format (encoded exactly as a one-step launch would store it).
+// Halo nodes across a periodic face are the wrapped nodes; halo nodes behind
+// a wall are not needed (step 2 takes the wall rule there).  Step 2 pulls
+// f(t+2) from LDS, applies the same wall rule, emits the fields and writes
+// f*(t+2) to HBM.  The fields of step 1 are not written: the emission buffer
+// holds the fields of the latest step, and step 2 overwrites the same
+// channels.  Every population, field and emitted value is bitwise that of
+// two one-step launches; HBM traffic per step drops from one read and one
+// write of the state to about half of that plus the halo re-reads
+// ((64 + 2)(TY + 2) / (64 TY) of a read per two steps).
+// The caller keeps f*(t+1) out of HBM, so the buffer the read kernels pull
+// from is stale after this kernel until the next one-step launch.
+// k_tile and k_march take three and more steps; of two this kernel is faster
+// (8192^2 FP32 1.55 ms and strips of two steps 2.00; FP16 1.02 and 1.25; FP64
+// 4096^2 0.79 and tiles 1.01).
+template <class L, int ST>
+struct Step2Lds {
+    static constexpr int NE = kF2W * (Fuse2Rows<ST>::TY + 2);
+    typename Store<ST>::T v[L::NS * L::Q * NE];
+};
+
+template <class L, int ST, bool EMIT, bool MASK, bool NTST = false, bool WIDE = true>
+__device__ __forceinline__ void step2_tile(const KCase &p, int gx, int gy, int tile, const typename Store<ST>::T *__restrict__ src,
+                                           typename Store<ST>::T *__restrict__ dst, const uint8_t *__restrict__ links,
+                                           uint32_t fields, typename Store<ST>::C *__restrict__ out,
+                                           typename Store<ST>::T *__restrict__ lds)
+{
+    static_assert(L::D == 2, "two-step tiles are two-dimensional");
+    using S = Store<ST>;
+    using C = typename S::C;
+    constexpr int TY = Fuse2Rows<ST>::TY, NT = Fuse2Rows<ST>::NT;
+    constexpr int W = kF2W, NE = kF2W * (TY + 2);
+    int tx, ty;
+    strip_tile(tile, gx, gy, tx, ty);
+    const int x0 = tx * kF2X, y0 = ty * TY;
+    const int tid = threadIdx.x;
+    const long long nodes = (long long)p.nx * p.ny;
+
+    // step 1: t -> t+1 on the tile and its halo, into LDS.  A thread owns
+    // the halo-tile nodes tid, tid + 256, ...; G of them are pulled before
+    // any is computed, so that (FP32, FP64) G nodes' loads are in flight
+    // together (occupancy is bounded by LDS, not by registers).  The 16-bit
+    // formats decode each node's values before the next node's loads.
+    constexpr int K1 = (NE + NT - 1) / NT;
+    constexpr int G = K1 < 3 ? K1 : 3;
+#pragma unroll
+    for (int k0 = 0; k0 < K1; k0 += G) {
+        Node<L, C> n[G];
+        bool fluid[G];
+        // issue this batch's loads ahead of other waves' arithmetic
+        __builtin_amdgcn_s_setprio(2);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int e = tid + (k0 + g) * NT;
+            fluid[g] = false;
+            if (k0 + g >= K1 || e >= NE) continue;
+            const int ex = e % W, ey = e / W;
+            int x = x0 - 1 + ex, y = y0 - 1 + ey;
+            if (x < 0 || x >= p.nx) {
+                if (p.bc[x < 0 ? 0 : 1] == MDF_WALL) continue;
+                x = ((x % p.nx) + p.nx) % p.nx;
+            }
+            if (y < 0 || y >= p.ny) {
+                if (p.bc[y < 0 ? 2 : 3] == MDF_WALL) continue;
+                y = ((y % p.ny) + p.ny) % p.ny;
+            }
+            fluid[g] = gather<L, ST, MASK, true, WIDE>(p, src, links, x, y, 0, n[g]);   // false: solid node
+        }
+        __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (!fluid[g]) continue;
+            const int e = tid + (k0 + g) * NT;
+            Moments<L, C> m;
+            moments<L, C>(p, n[g], m);
+            if (EMIT && (fields & MDF_FIELD_ACCUMULATE)) {
+                // accumulated fields count every step: step 1's fields of
+                // the tile's own nodes (not of its halo)
+                const int ex = e % W, ey = e / W;
+                const int x = x0 - 1 + ex, y = y0 - 1 + ey;
+                if (ex >= 1 && ex <= kF2X && ey >= 1 && ey <= TY && x < p.nx && y < p.ny)
+                    write_fields<L, C>(p, n[g], m, fields, out, grid_ix<WIDE>(x, y, 0, p.ny, p.nx), nodes);
+            }
+#pragma unroll
+            for (int a = 0; a < L::NS; ++a) {
+                C fo[L::Q];
+                collide_fused<L, C>(p, n[g], m, a, fo, m.fb[a + L::A0]);
+#pragma unroll
+                for (int i = 0; i < L::Q; ++i)
+                    lds[(a * L::Q + i) * NE + e] = S::encode(fo[i], rest_value<L, C>(p, a, i), p.inv_scale);
+            }
+        }
+    }
+    __syncthreads();
+
+    // step 2: t+1 -> t+2 on the tile, from LDS to HBM
+    for (int e = tid; e < kF2X * TY; e += NT) {
+        const int ox = e % kF2X, oy = e / kF2X;
+        const int x = x0 + ox, y = y0 + oy;
+        if (x >= p.nx || y >= p.ny) continue;
+        const auto own = grid_ix<WIDE>(x, y, 0, p.ny, p.pitch);
+        const auto node = grid_ix<WIDE>(x, y, 0, p.ny, p.nx);
+        const int le = (oy + 1) * W + (ox + 1);
+        unsigned lb = 0;
+        if (MASK) lb = *elem(links, own);
+        if (MASK && (lb & 0x80u)) {
+            if (EMIT) {
+                write_zero_fields<L, C>(fields, out, node, nodes);
+            }
+            continue;
+        }
+        Node<L, C> n;
+        load_sources<L, C>(p, (long long)y * p.nx + x, n);
+#pragma unroll
+        for (int i = 0; i < L::Q; ++i) {
+            int sx, sy, sz;            // (upstream values come from the LDS tile)
+            const int face = pull_face<L, MASK, true, WIDE>(p, links, lb, x, y, 0, i, sx, sy, sz);
+            const C w = C(L::w[i]);
+            if (face < 0) {
+                const int k = le - L::cx[i] - L::cy[i] * W;
+#pragma unroll
+                for (int a = 0; a < L::NS; ++a)
+                    n.f[a][i] = S::decode(lds[(a * L::Q + i) * NE + k], rest_value<L, C>(p, a, i), p.scale);
+            } else {
+                const int j = L::opp[i];
+#pragma unroll
+                for (int a = 0; a < L::NS; ++a) {
+                    const C v = S::decode(lds[(a * L::Q + j) * NE + le], rest_value<L, C>(p, a, j), p.scale);
+                    if (a + L::A0 == 0) {
+                        n.f[a][i] = v;
+                    } else {
+                        const int b = a + L::A0 - 1;
+                        const C uw = (face < 6) ? kpar<C>(p.wallu[face][b], p.walluf[face][b]) : C(0);
+                        n.f[a][i] = -v + C(2) * w * uw;
+                    }
+                }
+            }
+        }
+        Moments<L, C> m;
+        moments<L, C>(p, n, m);
+        if (EMIT) write_fields<L, C>(p, n, m, fields, out, node, nodes);
+#pragma unroll
+        for (int a = 0; a < L::NS; ++a) {
+            C fo[L::Q];
+            collide_fused<L, C>(p, n, m, a, fo, m.fb[a + L::A0]);
+#pragma unroll
+            for (int i = 0; i < L::Q; ++i) {
+                if (i >= qset<L>(a + L::A0)) continue;
+                S::template store_hint<NTST>(dst + plane_of<L>(a, i) * p.dstride, own, fo[i],
+                                             rest_value<L, C>(p, a, i), p.inv_scale);
+            }
+        }
+    }
+}
+
+template <class L, int ST, bool EMIT, bool MASK, bool NTST = false, bool WIDE = true>
+__global__ void __launch_bounds__(Fuse2Rows<ST>::NT)
+k_step2(KCase p, Tiling tl, const typename Store<ST>::T *__restrict__ src, typename Store<ST>::T *__restrict__ dst,
+        const uint8_t *__restrict__ links, uint32_t fields, typename Store<ST>::C *__restrict__ out)
+{
+    __shared__ Step2Lds<L, ST> lds;
+    step2_tile<L, ST, EMIT, MASK, NTST, WIDE>(p, tl.gx, tl.gy, block_tile(tl), src, dst, links, fields, out, lds.v);
+}
+
+// Batched two steps per launch: the persistent walk of k_step_batch over
+// the flat list of the active cases' two-step tiles (prefix offsets
+// tile_start3, total meta[3]).
+template <class L, int ST, bool EMIT, bool MASK, bool NTST = false, bool WIDE = true>
+__global__ void __launch_bounds__(Fuse2Rows<ST>::NT)
+k_step2_batch(const BatchEntry *__restrict__ tab, const int *__restrict__ meta,
+              const int *__restrict__ tile_start3, const int *__restrict__ active, int parity, uint32_t fields,
+              int groups)
+{
+    __shared__ Step2Lds<L, ST> lds;
+    const int nact = meta[0], total = meta[3];
+    const int G = gridDim.x;
+    const int ng = (groups > 1 && G % groups == 0) ? groups : 1;
+    const int g = blockIdx.x % ng, per = G / ng, slot = blockIdx.x / ng;
+    const int band_lo = (int)((long long)total * g / ng), band_hi = (int)((long long)total * (g + 1) / ng);
+    for (int t = band_lo + slot; t < band_hi; t += per) {
+        int lo = 0, hi = nact - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (tile_start3[mid] <= t) lo = mid;
+            else hi = mid - 1;
+        }
+        const BatchEntry &e = tab[active[lo]];
+        const int sel = (e.cur + parity) & 1;
+        using T = typename Store<ST>::T;
+        using C = typename Store<ST>::C;
+        step2_tile<L, ST, EMIT, MASK, NTST, WIDE>(e.p, e.gx2, e.gy2, t - tile_start3[lo],
+                                                  static_cast<const T *>(e.pop[sel]),
+                                                  static_cast<T *>(e.pop[sel ^ 1]), e.links, fields,
+                                                  static_cast<C *>(e.out), lds.v);
+        __syncthreads();   // the next tile's step 1 overwrites the LDS this tile's step 2 reads
+    }
+}
+
 // ----------------------------------------------------------------- two steps per pass (3D, axis links)
 
 // Output tile of k_step2z per storage: TX x TY nodes of an x-y plane, one
@@ -1635,8 +1878,7 @@ __device__ __forceinline__ void step2z_plane2(const KCase &p, typename Store<ST>
 // links.  Every population, field and emitted value is bitwise that of two
 // one-step launches; the state crosses HBM once per two steps, plus the
 // halo ring ((TX + TY) 2 / (TX TY) of a read) and the two chunk-end planes
-// (2 / zc of a read).  f*(t+1) never reaches HBM: the buffer the
-// read kernels pull from is stale until the next one-step launch.
+// (2 / zc of a read).  Like k_step2, f*(t+1) never reaches HBM.
 template <class L, int ST, bool EMIT, bool MASK, bool NTST = false, bool WIDE = true>
 __global__ void __launch_bounds__(Fuse2Z<ST>::TX * Fuse2Z<ST>::TY, Fuse2Z<ST>::MINW)
 k_step2z(KCase p, Tiling tl, const typename Store<ST>::T *__restrict__ src, typename Store<ST>::T *__restrict__ dst,
@@ -1962,9 +2204,9 @@ hipError_t step2_dispatch(const KCase &p, const CaseBufs &b, int src, uint32_t f
     using S = Store<ST>;
     using T = typename S::T;
     using C = typename S::C;
-    if constexpr (L::DIAG || L::D != 3) {
+    if constexpr (L::DIAG) {
         return hipErrorInvalidValue;
-    } else {
+    } else if constexpr (L::D == 3) {
         const T *in = static_cast<const T *>(b.pop[src]);
         T *o = static_cast<T *>(b.pop[src ^ 1]);
         C *emit = static_cast<C *>(out);
@@ -1990,6 +2232,30 @@ hipError_t step2_dispatch(const KCase &p, const CaseBufs &b, int src, uint32_t f
         else { if (emit_on) MDF_STEP2Z_LAUNCH(true, false); else MDF_STEP2Z_LAUNCH(false, false); }
 #undef MDF_STEP2Z_LAUNCH
 #undef MDF_STEP2Z_LAUNCH1
+        return hipGetLastError();
+    } else {
+        const T *in = static_cast<const T *>(b.pop[src]);
+        T *o = static_cast<T *>(b.pop[src ^ 1]);
+        C *emit = static_cast<C *>(out);
+        Tiling tl;
+        tl.gx = (p.nx + kF2X - 1) / kF2X;
+        tl.gy = (p.ny + Fuse2Rows<ST>::TY - 1) / Fuse2Rows<ST>::TY;
+        tl.nb = tl.gx * tl.gy;
+        tl.groups = s.groups > 1 ? s.groups : 1;
+        const bool emit_on = (fields != 0) && out != nullptr;
+        const bool mask = b.links != nullptr;
+#define MDF_STEP2_LAUNCH1(E, M, N, X)                                                                      \
+    hipLaunchKernelGGL((k_step2<L, ST, E, M, N, X>), dim3(tl.nb), dim3(Fuse2Rows<ST>::NT), 0, stream, p, tl, in, o, \
+                       b.links, fields, emit)
+#define MDF_STEP2_LAUNCH(E, M)                                                                     \
+    do {                                                                                           \
+        if (!p.ntstore) MDF_STEP2_LAUNCH1(E, M, false, true);                                      \
+        else MDF_STEP2_LAUNCH1(E, M, true, false);                                                 \
+    } while (0)
+        if (mask) { if (emit_on) MDF_STEP2_LAUNCH(true, true); else MDF_STEP2_LAUNCH(false, true); }
+        else { if (emit_on) MDF_STEP2_LAUNCH(true, false); else MDF_STEP2_LAUNCH(false, false); }
+#undef MDF_STEP2_LAUNCH
+#undef MDF_STEP2_LAUNCH1
         return hipGetLastError();
     }
 }
@@ -2177,6 +2443,43 @@ hipError_t march_batch_dispatch(const BatchLaunch &bl, bool emit, hipStream_t st
 }
 
 template <class L, int ST>
+hipError_t batch2_dispatch(const BatchLaunch &bl, bool emit, hipStream_t stream)
+{
+    if constexpr (L::D != 2 || L::DIAG) {
+        return hipErrorInvalidValue;
+    } else {
+        const dim3 grid(bl.grid, 1, 1), block(Fuse2Rows<ST>::NT, 1, 1);
+#define MDF_BATCH2_LAUNCH1(E, M, N, X)                                                                    \
+    hipLaunchKernelGGL((k_step2_batch<L, ST, E, M, N, X>), grid, block, 0, stream, bl.tab, bl.meta, bl.tile_start3, \
+                       bl.active, bl.parity, bl.fields, bl.shape.groups)
+#define MDF_BATCH2_LAUNCH(E, M)                                                                    \
+    do {                                                                                           \
+        if (!bl.ntstore) MDF_BATCH2_LAUNCH1(E, M, false, true);                                    \
+        else MDF_BATCH2_LAUNCH1(E, M, true, false);                                                \
+    } while (0)
+        if (bl.mask) { if (emit) MDF_BATCH2_LAUNCH(true, true); else MDF_BATCH2_LAUNCH(false, true); }
+        else { if (emit) MDF_BATCH2_LAUNCH(true, false); else MDF_BATCH2_LAUNCH(false, false); }
+#undef MDF_BATCH2_LAUNCH
+#undef MDF_BATCH2_LAUNCH1
+        return hipGetLastError();
+    }
+}
+
+template <class L, int ST>
+hipError_t batch2_capacity(bool mask, int *blocks_per_cu)
+{
+    if constexpr (L::D != 2 || L::DIAG) {
+        return hipErrorInvalidValue;
+    } else {
+        if (mask)
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_step2_batch<L, ST, true, true>,
+                                                                Fuse2Rows<ST>::NT, 0);
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_step2_batch<L, ST, true, false>,
+                                                            Fuse2Rows<ST>::NT, 0);
+    }
+}
+
+template <class L, int ST>
 hipError_t batch_capacity(LaunchShape shape, bool mask, int *blocks_per_cu)
 {
     // resident blocks per CU of the heaviest variant (emit + check)
@@ -2264,9 +2567,23 @@ hipError_t op_march_batch(int storage, const BatchLaunch &bl, bool emit, hipStre
 }
 
 template <class L>
+hipError_t op_batch2(int storage, const BatchLaunch &bl, bool emit, hipStream_t stream)
+{
+    MDF_DISPATCH_LAT(L, storage, batch2_dispatch, bl, emit, stream)
+    return hipErrorInvalidValue;
+}
+
+template <class L>
 hipError_t op_batch_cap(int storage, LaunchShape shape, bool mask, int *blocks_per_cu)
 {
     MDF_DISPATCH_LAT(L, storage, batch_capacity, shape, mask, blocks_per_cu)
+    return hipErrorInvalidValue;
+}
+
+template <class L>
+hipError_t op_batch2_cap(int storage, bool mask, int *blocks_per_cu)
+{
+    MDF_DISPATCH_LAT(L, storage, batch2_capacity, mask, blocks_per_cu)
     return hipErrorInvalidValue;
 }
 
@@ -2290,7 +2607,9 @@ LatOps make_lat_ops()
     o.init = op_init<L>;
     o.batch = op_batch<L>;
     o.march_batch = op_march_batch<L>;
+    o.batch2 = op_batch2<L>;
     o.batch_cap = op_batch_cap<L>;
+    o.batch2_cap = op_batch2_cap<L>;
     o.links = op_links<L>;
     o.cs2 = L::cs2;
     return o;

@@ -116,6 +116,16 @@ int read_blocks(const KCase &p, LaunchShape s)
     return tiling_of(p, s, 1).nb;
 }
 
+int step2_rows(int storage)
+{
+    switch (storage) {
+    case MDF_F64: return Fuse2Rows<MDF_F64>::TY;
+    case MDF_F32: return Fuse2Rows<MDF_F32>::TY;
+    case MDF_F16DEV: return Fuse2Rows<MDF_F16DEV>::TY;
+    default: return Fuse2Rows<MDF_BF16DEV>::TY;
+    }
+}
+
 // Strips for FP32 and the 16-bit formats beyond the Infinity Cache, where
 // the traffic per step counts (4096^2: FP32 116 us per step in strips and 166
 // in tiles, FP16 99 and 125); tiles inside it (1024^2: FP32 9.8 and 7.5 us,
@@ -173,7 +183,7 @@ hipError_t launch_step2(int lattice, int storage, const KCase &p, const CaseBufs
                         void *out, LaunchShape shape, hipStream_t stream)
 {
     const LatOps *o = ops_of(lattice);
-    if (!o || !axis_links(lattice) || two_d(lattice)) return hipErrorInvalidValue;
+    if (!o || !axis_links(lattice) || (two_d(lattice) && p.nz != 1)) return hipErrorInvalidValue;
     return o->step2(storage, p, b, src, fields, out, shape, stream);
 }
 
@@ -214,6 +224,20 @@ hipError_t launch_finalize(const CaseBufs &b, int nblocks, hipStream_t stream)
 {
     hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, stream, b.partial, nblocks, b.result);
     return hipGetLastError();
+}
+
+hipError_t launch_step2_batch(int lattice, int storage, const BatchLaunch &bl, hipStream_t stream)
+{
+    const LatOps *o = ops_of(lattice);
+    if (!o || !two_d(lattice)) return hipErrorInvalidValue;
+    return o->batch2(storage, bl, bl.fields != 0, stream);
+}
+
+hipError_t batch2_blocks_per_cu(int lattice, int storage, bool mask, int *blocks_per_cu)
+{
+    const LatOps *o = ops_of(lattice);
+    if (!o || !two_d(lattice)) return hipErrorInvalidValue;
+    return o->batch2_cap(storage, mask, blocks_per_cu);
 }
 
 hipError_t launch_march_batch(int lattice, int storage, const BatchLaunch &bl, hipStream_t stream)

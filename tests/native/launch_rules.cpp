@@ -14,6 +14,9 @@ int main()
         if (!std::strcmp(what, "most")) {               // cover storage mask gen
             if (std::scanf("%d%d%d%d", a, a + 1, a + 2, a + 3) != 4) return 1;
             std::printf("%d\n", mdf::march_max(mdf::Cover(a[0]), a[1], a[2] != 0, a[3] != 0));
+        } else if (!std::strcmp(what, "next")) {        // left most
+            if (std::scanf("%d%d", a, a + 1) != 2) return 1;
+            std::printf("%d\n", mdf::march_next(a[0], a[1]));
         } else {
             return 1;
         }

@@ -72,3 +72,64 @@ def test_forced_batches(storage, sizes):
         stream.synchronize()
     assert all(torch.isfinite(t).all() for t in out[0])
     assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("storage,nx,ny", GRIDS)
+@pytest.mark.parametrize("mask", [False, True])
+def test_calls_of_three_steps(storage, nx, ny, mask):
+    """Three steps a call, two of them in one launch: plain, accumulating (both
+    steps count) and emitting, and a force field."""
+    print(f"[gpu] three steps {storage} {nx}x{ny} mask={mask}", flush=True)
+    out = []
+    for form in (0, 2):
+        rng = np.random.default_rng(nx)
+        data = _init(nx, ny, storage)
+        solid = (rng.random((ny, nx)) < 0.05).astype(np.uint8) if mask else None
+        if mask:
+            data[:, torch.as_tensor(solid).bool()] = 0.0
+        s = mdf.Solver(_spec(nx, ny, mask, True, rng), storage=storage, solid=[solid] if mask else None,
+                       init=("fields", [data]), u_ref=0.1)
+        s.set_launch(64, 4, 8, form)
+        s.step(3)
+        got = [s.populations()]
+        acc = [torch.zeros_like(t) for t in s.new_field_buffers(MOM)]
+        s.step_emit(3, MOM | mdf.FIELD_ACCUMULATE, acc)
+        got += acc + s.step_emit(3, MOM)
+        s.set_force_field(torch.as_tensor(rng.uniform(-1e-4, 1e-4, (2, ny, nx))))
+        s.step(3)
+        out.append(got + [s.gradients(mdf.FIELD_ALL)])
+    assert all(torch.isfinite(t).all() for t in out[0])
+    assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("storage,sizes", [("f64", [(70, 45), (33, 90), (1, 7)]), ("f32", [(1200, 1100), (64, 64)])])
+@pytest.mark.parametrize("mask", [False, True])
+def test_batches_of_three_steps(storage, sizes, mask):
+    """Batched two-step launches, in chunks of three and six steps, while cases
+    are switched off and on."""
+    print(f"[gpu] three steps batch {storage} {sizes} mask={mask}", flush=True)
+    stream = torch.cuda.Stream()
+    out = []
+    for form in (0, 2):
+        rng = np.random.default_rng(7)
+        specs = [_spec(nx, ny, True, k % 2 == 0, rng) for k, (nx, ny) in enumerate(sizes)]
+        init = [_init(nx, ny, storage, k) for k, (nx, ny) in enumerate(sizes)]
+        solid = None
+        if mask:
+            solid = [(rng.random((ny, nx)) < 0.05).astype(np.uint8) if k == 0 else None
+                     for k, (nx, ny) in enumerate(sizes)]
+            init[0][:, torch.as_tensor(solid[0]).bool()] = 0.0
+        with torch.cuda.stream(stream):
+            s = mdf.Solver(specs, storage=storage, solid=solid, init=("fields", init), u_ref=0.1, stream=stream)
+            s.set_launch(64, 4, 8, form)
+            s.step(3)
+            s.set_active([k != 1 for k in range(len(sizes))])
+            s.step(6)
+            s.set_active([1] * len(sizes))
+            for _ in range(3):
+                s.step(6)
+            res = s.run_steady(1e-15, 3, 9)
+            out.append([s.populations(k) for k in range(len(sizes))] + [torch.as_tensor(res[1])] + s.step_emit(3, MOM))
+        stream.synchronize()
+    assert all(torch.isfinite(t.double()).all() for t in out[0])
+    assert all(torch.equal(a, b) for a, b in zip(*out))

@@ -38,3 +38,23 @@ def test_five_steps_only_where_the_kernel_keeps_its_registers(ask):
     got = ask(*[("most",) + q for q in qs])
     for (c, s, m, g), (most,) in zip(qs, got):
         assert most == (5 if (c, s, m, g) == (STRIPS, mdf.F32, 0, 0) else 4), (c, s, m, g)
+
+
+def test_steps_of_a_call(ask):
+    """A call's launches take all of its steps, at most `most` each, the last
+    one alone, and no others alone but in a call of two: the two steps before
+    the last of three run as one launch."""
+    ks = {}
+    for most in (4, 5):
+        nxt = [int(v[0]) for v in ask(*[("next", left, most) for left in range(1, 301)])]
+        for n in range(1, 301):
+            seq, left = [], n
+            while left > 0:
+                seq.append(nxt[left - 1])
+                left -= seq[-1]
+            assert left == 0 and seq[-1] == 1 and max(seq) <= most, (n, most, seq)
+            assert seq[:-1].count(1) == (1 if n == 2 else 0), (n, most, seq)
+            assert len(seq) - 1 == (n - 1 + most - 1) // most, (n, most, seq)
+            ks[n, most] = seq
+    assert ks[3, 4] == ks[3, 5] == [2, 1]
+    assert ks[6, 4] == [3, 2, 1] and ks[6, 5] == [5, 1] and ks[5, 4] == [4, 1]
