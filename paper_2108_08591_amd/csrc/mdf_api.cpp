@@ -131,7 +131,7 @@ struct CaseLayout {
 
 // Context-wide regions of the workspace (batched launches).
 struct SharedLayout {
-    size_t table, meta, tile_start, tile_start2, tile_start3, active;
+    size_t table, meta, tile_start, tile_start2, active;
 };
 
 // Blocks of the largest grid any allowed launch shape produces
@@ -202,9 +202,7 @@ size_t layout(int lattice, int storage, const mdf_case *cases, int ncases, bool 
     sh.tile_start = off;
     off = align256(off + size_t(ncases + 1) * sizeof(int));
     sh.tile_start2 = off;
-    off = align256(off + size_t(ncases + 1) * sizeof(int));
-    sh.tile_start3 = off;
-    off = align256(off + size_t(ncases + 1) * sizeof(int));
+    off = align256(off + 2 * size_t(ncases + 1) * sizeof(int));
     sh.active = off;
     off = align256(off + size_t(ncases) * sizeof(int));
     if (shared) *shared = sh;
@@ -255,11 +253,10 @@ struct mdf_ctx {
     bool any_mask = false;
     mdf::Cover cover = mdf::kCoverSmall; // units of launches of several steps
     mdf::BatchEntry *d_tab = nullptr;
-    int *d_meta = nullptr, *d_tile_start = nullptr, *d_tile_start2 = nullptr, *d_tile_start3 = nullptr,
-        *d_active = nullptr;
+    int *d_meta = nullptr, *d_tile_start = nullptr, *d_tile_start2 = nullptr, *d_active = nullptr;
     double *d_results = nullptr;
     std::vector<mdf::BatchEntry> h_tab;
-    std::vector<int> h_tile_start, h_tile_start2, h_tile_start3, h_active, h_meta;
+    std::vector<int> h_tile_start, h_tile_start2, h_active, h_meta;
     std::vector<double> h_results;
     int launches_since_upload = 0;       // buffer parity of the uploaded table
     int uploaded_fields = -1;
@@ -498,11 +495,12 @@ mdf_status batch_upload(mdf_ctx *ctx, const std::vector<int> &active, uint32_t f
     }
     if (total > 0x7fffffffLL) return fail(ctx, MDF_EINVAL, "batch has too many tiles");
     ctx->h_tile_start[active.size()] = int(total);
-    ctx->h_tile_start2.assign(active.size() + 1, 0);
-    ctx->h_tile_start3.assign(active.size() + 1, 0);
+    // of launches of several steps and, from entry n + 1 on, of two: one copy
+    ctx->h_tile_start2.assign(2 * (size_t(n) + 1), 0);
+    int *const start3 = ctx->h_tile_start2.data() + n + 1;
     long long total2 = 0, total3 = 0;
     for (size_t i = 0; i < active.size(); ++i) {
-        ctx->h_tile_start3[i] = int(total3);
+        start3[i] = int(total3);
         total3 += ctx->h_tab[active[i]].ntiles2;
         ctx->h_tile_start2[i] = int(total2);
         const mdf::MarchGrid &g = ctx->h_tab[active[i]].march;
@@ -510,7 +508,7 @@ mdf_status batch_upload(mdf_ctx *ctx, const std::vector<int> &active, uint32_t f
     }
     if (units > 0x7fffffffLL || total3 > 0x7fffffffLL) return fail(ctx, MDF_EINVAL, "batch has too many tiles");
     ctx->h_tile_start2[active.size()] = int(total2);
-    ctx->h_tile_start3[active.size()] = int(total3);
+    start3[active.size()] = int(total3);
     ctx->h_meta = {int(active.size()), int(total), int(total2), int(total3)};
     hipError_t e = hipMemcpyAsync(ctx->d_tab, ctx->h_tab.data(), sizeof(mdf::BatchEntry) * n, hipMemcpyHostToDevice, st);
     if (e == hipSuccess)
@@ -519,10 +517,7 @@ mdf_status batch_upload(mdf_ctx *ctx, const std::vector<int> &active, uint32_t f
         e = hipMemcpyAsync(ctx->d_tile_start, ctx->h_tile_start.data(), sizeof(int) * (active.size() + 1),
                            hipMemcpyHostToDevice, st);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(ctx->d_tile_start2, ctx->h_tile_start2.data(), sizeof(int) * (active.size() + 1),
-                               hipMemcpyHostToDevice, st);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(ctx->d_tile_start3, ctx->h_tile_start3.data(), sizeof(int) * (active.size() + 1),
+            e = hipMemcpyAsync(ctx->d_tile_start2, ctx->h_tile_start2.data(), sizeof(int) * 2 * (size_t(n) + 1),
                                hipMemcpyHostToDevice, st);
         if (e == hipSuccess)
             e = hipMemcpyAsync(ctx->d_active, active.data(), sizeof(int) * active.size(), hipMemcpyHostToDevice, st);
@@ -542,7 +537,7 @@ mdf::BatchLaunch batch_args(mdf_ctx *ctx, uint32_t fields, int grid)
     bl.meta = ctx->d_meta;
     bl.tile_start = ctx->d_tile_start;
     bl.tile_start2 = ctx->d_tile_start2;
-    bl.tile_start3 = ctx->d_tile_start3;
+    bl.tile_start3 = ctx->d_tile_start2 + ctx->ncases + 1;
     bl.active = ctx->d_active;
     bl.parity = 0;
     bl.fields = fields;
@@ -758,7 +753,6 @@ mdf_status mdf_init(mdf_ctx **out, mdf_lattice lattice, mdf_storage storage, con
     ctx->d_meta = reinterpret_cast<int *>(ws + shl.meta);
     ctx->d_tile_start = reinterpret_cast<int *>(ws + shl.tile_start);
     ctx->d_tile_start2 = reinterpret_cast<int *>(ws + shl.tile_start2);
-    ctx->d_tile_start3 = reinterpret_cast<int *>(ws + shl.tile_start3);
     ctx->d_active = reinterpret_cast<int *>(ws + shl.active);
     ctx->d_results = reinterpret_cast<double *>(ws + lay[0].result);
     ctx->h_results.assign(size_t(ncases) * mdf::kNRed, 0.0);

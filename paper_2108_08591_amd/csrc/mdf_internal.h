@@ -114,7 +114,7 @@ struct BatchLaunch {
     const int *meta;        // device: {active cases, total tiles}
     const int *tile_start;  // device: prefix offsets of the active cases' tiles
     const int *tile_start2; // device: the same for the units of launches of several steps
-    const int *tile_start3; // device: the same for two-step tiles
+    const int *tile_start3; // device: the same for two-step tiles (follows tile_start2)
     const int *active;      // device: case ids of the active cases
     int parity;             // launches since the table upload, mod 2
     uint32_t fields;        // emitted fields (0: none)
