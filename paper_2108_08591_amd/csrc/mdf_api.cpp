@@ -229,10 +229,11 @@ size_t layout(int lattice, int storage, const mdf_case *cases, int ncases, bool 
 }  // namespace
 
 struct GraphKey {
-    int len, check, emit, parity, fuse;
+    int len, check, emit, parity, fuse, cover, units;
     bool operator==(const GraphKey &o) const
     {
-        return len == o.len && check == o.check && emit == o.emit && parity == o.parity && fuse == o.fuse;
+        return len == o.len && check == o.check && emit == o.emit && parity == o.parity && fuse == o.fuse &&
+               cover == o.cover && units == o.units;
     }
 };
 
@@ -251,7 +252,7 @@ struct mdf_ctx {
     // batched launches (ncases > 1)
     bool batched = false;
     bool any_mask = false;
-    mdf::Cover cover = mdf::kCoverSmall; // units of launches of several steps
+    mdf::Cover cover = mdf::kCoverSmall; // units of launches of several steps, by the nodes that they advance
     mdf::BatchEntry *d_tab = nullptr;
     int *d_meta = nullptr, *d_tile_start = nullptr, *d_tile_start2 = nullptr, *d_active = nullptr;
     double *d_results = nullptr;
@@ -260,7 +261,7 @@ struct mdf_ctx {
     std::vector<double> h_results;
     int launches_since_upload = 0;       // buffer parity of the uploaded table
     int uploaded_fields = -1;
-    int batch_units = 0;                 // units of all cases in launches of several steps
+    int batch_units = 0;                 // grid of launches of several steps of the uploaded cases
     int num_cu = 0;
     std::vector<std::pair<GraphKey, hipGraphExec_t>> graphs;
     bool use_graphs = true;
@@ -451,6 +452,27 @@ mdf_status batch_capacity_grid(mdf_ctx *ctx, int *grid)
     return MDF_OK;
 }
 
+// Bytes of one population buffer of a case.
+size_t pop_bytes_of(const mdf_ctx *ctx, int k)
+{
+    return size_t(lat_planes(ctx->lattice)) * size_t(ctx->kc[k].dstride) * storage_bytes(ctx->storage);
+}
+
+constexpr size_t kInfinityCacheBytes = size_t(256) << 20;
+
+// Units of launches of several steps of these cases, by their nodes and by
+// whether the launches find their populations in the Infinity Cache.
+mdf::Cover cover_of(const mdf_ctx *ctx, const std::vector<int> &cases)
+{
+    long long nodes = 0;
+    size_t pop = 0;
+    for (int k : cases) {
+        nodes += (long long)ctx->kc[k].nx * ctx->kc[k].ny * ctx->kc[k].nz;
+        pop += 2 * pop_bytes_of(ctx, k);
+    }
+    return mdf::march_cover(nodes, ctx->storage, pop > kInfinityCacheBytes);
+}
+
 // Fill the host mirror of the case table for the given active cases and
 // emission targets, and copy it to the device.  Waits for the copies.
 mdf_status batch_upload(mdf_ctx *ctx, const std::vector<int> &active, uint32_t fields, void *const *out,
@@ -458,6 +480,7 @@ mdf_status batch_upload(mdf_ctx *ctx, const std::vector<int> &active, uint32_t f
 {
     const int n = ctx->ncases;
     long long units = 0;                // of all cases, active or not
+    ctx->cover = cover_of(ctx, active);
     ctx->h_tab.resize(n);
     for (int k = 0; k < n; ++k) {
         mdf::BatchEntry &e = ctx->h_tab[k];
@@ -524,7 +547,7 @@ mdf_status batch_upload(mdf_ctx *ctx, const std::vector<int> &active, uint32_t f
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return device_error(ctx, e, "batch table upload");
-    ctx->batch_units = int(units);
+    ctx->batch_units = mdf::march_grid(total2, units);
     ctx->launches_since_upload = 0;
     ctx->uploaded_fields = int(fields);
     return MDF_OK;
@@ -604,7 +627,7 @@ mdf_status batch_steps(mdf_ctx *ctx, int nsteps, bool check, uint32_t fields, hi
         }
         return e;
     };
-    const GraphKey key{nsteps, check ? 1 : 0, int(fields), p0, fuse ? 1 : 0};
+    const GraphKey key{nsteps, check ? 1 : 0, int(fields), p0, fuse ? 1 : 0, int(ctx->cover), ctx->batch_units};
     hipGraphExec_t exec = nullptr;
     for (auto &g : ctx->graphs)
         if (g.first == key) exec = g.second;
@@ -790,12 +813,12 @@ mdf_status mdf_init(mdf_ctx **out, mdf_lattice lattice, mdf_storage storage, con
     // are written with a non-temporal hint (measured: +3.4-4.4 % on 8192^2
     // and 256^3 grids, -23 % on a 1024^2 grid that fits the cache).
     size_t pop_total = 0;
-    for (int k = 0; k < ncases; ++k)
-        pop_total += 2 * size_t(lat_planes(lattice)) * size_t(ctx->kc[k].dstride) * storage_bytes(storage);
-    const size_t kInfinityCacheBytes = size_t(256) << 20;
-    long long nodes = 0;
-    for (int k = 0; k < ncases; ++k) nodes += (long long)cases[k].nx * cases[k].ny * cases[k].nz;
-    ctx->cover = mdf::march_cover(nodes, storage, pop_total > kInfinityCacheBytes);
+    std::vector<int> all;
+    for (int k = 0; k < ncases; ++k) {
+        pop_total += 2 * pop_bytes_of(ctx, k);
+        all.push_back(k);
+    }
+    ctx->cover = cover_of(ctx, all);
     for (int k = 0; k < ncases; ++k) ctx->kc[k].ntstore = pop_total > kInfinityCacheBytes ? 1 : 0;
     *out = ctx;
     return MDF_OK;
@@ -1120,7 +1143,7 @@ mdf_status mdf_population_buffer(const mdf_ctx *ctx, int32_t case_id, int32_t wh
     if (which != 0 && which != 1) return fail(c, MDF_EINVAL, "mdf_population_buffer: which must be 0 or 1");
     if (!ptr || !bytes) return fail(c, MDF_EINVAL, "mdf_population_buffer: NULL output");
     *ptr = ctx->bufs[case_id].pop[which == 0 ? ctx->cur[case_id] : ctx->cur[case_id] ^ 1];
-    *bytes = size_t(lat_planes(ctx->lattice)) * size_t(ctx->kc[case_id].dstride) * storage_bytes(ctx->storage);
+    *bytes = pop_bytes_of(ctx, case_id);
     return MDF_OK;
 }
 
@@ -1157,11 +1180,6 @@ struct StateCase {
 
 const char kStateMagic[8] = {'M', 'D', 'F', 'S', 'T', 'A', 'T', '1'};
 
-size_t case_pop_bytes(const mdf_ctx *ctx, int k)
-{
-    return size_t(lat_planes(ctx->lattice)) * size_t(ctx->kc[k].dstride) * storage_bytes(ctx->storage);
-}
-
 size_t case_snap_bytes(const mdf_ctx *ctx, int k)
 {
     const KCase &p = ctx->kc[k];
@@ -1171,7 +1189,7 @@ size_t case_snap_bytes(const mdf_ctx *ctx, int k)
 size_t state_bytes(const mdf_ctx *ctx)
 {
     size_t n = sizeof(StateHeader) + size_t(ctx->ncases) * sizeof(StateCase);
-    for (int k = 0; k < ctx->ncases; ++k) n += 2 * case_pop_bytes(ctx, k) + case_snap_bytes(ctx, k);
+    for (int k = 0; k < ctx->ncases; ++k) n += 2 * pop_bytes_of(ctx, k) + case_snap_bytes(ctx, k);
     return n;
 }
 
@@ -1214,7 +1232,7 @@ mdf_status mdf_save(mdf_ctx *ctx, void *dst, size_t bytes, void *stream)
         c.time = ctx->time[k];
         c.snap_time = ctx->snap_time[k];
         c.enabled = ctx->enabled[k];
-        c.pop_bytes = case_pop_bytes(ctx, k);
+        c.pop_bytes = pop_bytes_of(ctx, k);
         c.snap_bytes = case_snap_bytes(ctx, k);
         std::memcpy(head.data() + sizeof h + size_t(k) * sizeof c, &c, sizeof c);
         // the buffer holding f*(t) first, then the one the read kernels pull from
@@ -1262,7 +1280,7 @@ mdf_status mdf_load(mdf_ctx *ctx, const void *src, size_t bytes, void *stream)
         const StateCase &c = cs[k];
         const KCase &p = ctx->kc[k];
         if (c.nx != p.nx || c.ny != p.ny || c.nz != p.nz || c.pitch != p.pitch ||
-            c.pop_bytes != case_pop_bytes(ctx, k) || c.snap_bytes != case_snap_bytes(ctx, k))
+            c.pop_bytes != pop_bytes_of(ctx, k) || c.snap_bytes != case_snap_bytes(ctx, k))
             return fail(ctx, MDF_EINVAL, "mdf_load: case %d was %d x %d x %d, context has %d x %d x %d", k, c.nx,
                         c.ny, c.nz, p.nx, p.ny, p.nz);
     }

@@ -195,9 +195,7 @@ hipError_t batch2_blocks_per_cu(int lattice, int storage, bool mask, int *blocks
 int step2_rows(int storage);
 // Batched launch of bl.steps steps over the list of units (the 2D lattices with axis links).
 hipError_t launch_march_batch(int lattice, int storage, const BatchLaunch &bl, hipStream_t stream);
-// Units of launches of several steps of a context with `nodes` nodes in all
-// its cases, and the units of one case.
-Cover march_cover(long long nodes, int storage, bool beyond_cache);
+// Units of one case in launches of several steps.
 MarchGrid march_plan(const KCase &p, int storage, Cover cover);
 hipError_t launch_finalize_batch(const BatchEntry *tab, const int *meta, const int *active, int nactive,
                                  hipStream_t stream);
@@ -209,6 +207,31 @@ double lattice_cs2(int lattice);
 // Blocks of one step launch / one read launch.
 int grid_blocks(const KCase &p, int storage, LaunchShape shape);
 int read_blocks(const KCase &p, LaunchShape shape);
+
+// Units of launches of several steps of cases with `nodes` nodes in all:
+// strips for FP32 and the 16-bit formats beyond the Infinity Cache, where
+// the traffic per step counts (4096^2: FP32 116 us per step in strips and 166
+// in tiles, FP16 99 and 125); tiles inside it (1024^2: FP32 9.8 and 7.5 us,
+// FP16 13.9 and 9.4) and for FP64 (4096^2 320 and 247 us, 1024^2 21.5 and
+// 13.4), small ones up to 73728 nodes (256^2: FP64 2.5 us per step in small and
+// 2.6 in large ones, FP32 1.7 and 1.9; 384^2: 4.0 and 3.1, 2.8 and 2.0).
+inline Cover march_cover(long long nodes, int storage, bool beyond_cache)
+{
+    if (nodes <= 73728) return kCoverSmall;
+    return storage != MDF_F64 && beyond_cache ? kCoverStrips : kCoverLarge;
+}
+
+// Blocks (or wavefronts, in strips) of a batched launch of several steps whose
+// running cases have `active` units, of `all` in the batch: the next power of
+// two, so that a captured launch serves many sets of running cases.  100 steps
+// of one running case of 512 x 128^2: FP16 1.53 ms and FP32 0.82 ms with the
+// units and the grid of the whole batch, 0.17 and 0.16 ms with its own.
+inline int march_grid(long long active, long long all)
+{
+    long long g = 1;
+    while (g < active) g *= 2;
+    return int(g < all ? g : all);
+}
 
 // Most steps of a launch of several steps: four, and five in FP32 strips
 // without obstacles, force field and Scheme II (21 steps, five and four at a

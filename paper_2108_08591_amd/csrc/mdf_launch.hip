@@ -126,18 +126,6 @@ int step2_rows(int storage)
     }
 }
 
-// Strips for FP32 and the 16-bit formats beyond the Infinity Cache, where
-// the traffic per step counts (4096^2: FP32 116 us per step in strips and 166
-// in tiles, FP16 99 and 125); tiles inside it (1024^2: FP32 9.8 and 7.5 us,
-// FP16 13.9 and 9.4) and for FP64 (4096^2 320 and 247 us, 1024^2 21.5 and
-// 13.4), small ones up to 73728 nodes (256^2: FP64 2.5 us per step in small and
-// 2.6 in large ones, FP32 1.7 and 1.9; 384^2: 4.0 and 3.1, 2.8 and 2.0).
-Cover march_cover(long long nodes, int storage, bool beyond_cache)
-{
-    if (nodes <= 73728) return kCoverSmall;
-    return storage != MDF_F64 && beyond_cache ? kCoverStrips : kCoverLarge;
-}
-
 // Strips have one column of halo per step on either side, or, in FP32, 8:
 // 48 columns written, whose rows start and end on 64-byte blocks, so that no
 // two strips write into the same block (8192^2, five steps: 2.17 ms per pass

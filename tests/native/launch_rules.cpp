@@ -17,6 +17,12 @@ int main()
         } else if (!std::strcmp(what, "next")) {        // left most
             if (std::scanf("%d%d", a, a + 1) != 2) return 1;
             std::printf("%d\n", mdf::march_next(a[0], a[1]));
+        } else if (!std::strcmp(what, "grid")) {        // active all
+            if (std::scanf("%d%d", a, a + 1) != 2) return 1;
+            std::printf("%d\n", mdf::march_grid(a[0], a[1]));
+        } else if (!std::strcmp(what, "cover")) {       // nodes storage beyond_cache
+            if (std::scanf("%d%d%d", a, a + 1, a + 2) != 3) return 1;
+            std::printf("%d\n", int(mdf::march_cover(a[0], a[1], a[2] != 0)));
         } else {
             return 1;
         }

@@ -133,3 +133,35 @@ def test_batches_of_three_steps(storage, sizes, mask):
         stream.synchronize()
     assert all(torch.isfinite(t.double()).all() for t in out[0])
     assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("storage,sizes", [("f32", [(1200, 1100), (64, 64), (1000, 1001), (300, 290)]),
+                                           ("f16dev", [(57, 61), (1700, 1600), (500, 410), (1500, 1300)])])
+def test_units_follow_the_running_cases(storage, sizes):
+    """A batch beyond the Infinity Cache whose running cases go from all of them
+    (strips) to a middle one (large tiles) and a small one (small tiles) and
+    back, each set twice with chunks of one length, so that captured launches
+    of several grids are replayed."""
+    print(f"[gpu] units of running cases {storage}", flush=True)
+    sets = [[1, 1, 1, 1], [0, 0, 0, 1], [1, 1, 1, 1], [0, 1, 0, 0], [1, 0, 0, 0], [0, 0, 1, 1], [1, 0, 0, 0],
+            [0, 1, 0, 0], [0, 0, 0, 1], [1, 1, 1, 1]]
+    stream = torch.cuda.Stream()
+    out = []
+    for form in (0, 2):
+        rng = np.random.default_rng(11)
+        specs = [_spec(nx, ny, k % 2 == 0, True, rng) for k, (nx, ny) in enumerate(sizes)]
+        init = [_init(nx, ny, storage, k) for k, (nx, ny) in enumerate(sizes)]
+        with torch.cuda.stream(stream):
+            s = mdf.Solver(specs, storage=storage, init=("fields", init), u_ref=0.1, stream=stream)
+            s.set_launch(64, 4, 8, form)
+            for active in sets:
+                s.set_active(active)
+                s.step(9)
+                s.step(9)
+            s.set_active([1] * 4)
+            out.append([s.populations(k) for k in range(4)] + s.step_emit(9, MOM))
+            stats = s.graph_stats()
+        stream.synchronize()
+        assert stats["failed"] == 0 and stats["replayed"] == 2 * len(sets) + 1
+    assert all(torch.isfinite(t).all() for t in out[0])
+    assert all(torch.equal(a, b) for a, b in zip(*out))

@@ -58,3 +58,16 @@ def test_steps_of_a_call(ask):
             ks[n, most] = seq
     assert ks[3, 4] == ks[3, 5] == [2, 1]
     assert ks[6, 4] == [3, 2, 1] and ks[6, 5] == [5, 1] and ks[5, 4] == [4, 1]
+
+
+def test_units_of_a_batch(ask):
+    """The grid of a batched launch covers the running cases' units, at most
+    twice over and never more than all units; small cases run in small tiles
+    whatever else the batch holds."""
+    qs = [(a, b) for b in (1, 7, 93000, 2 ** 30 + 5) for a in (1, 2, 3, 5, 64, 46501, 92999, 93000, 2 ** 30 + 5) if a <= b]
+    for (a, b), (g,) in zip(qs, ask(*[("grid",) + q for q in qs])):
+        assert a <= g <= b and (g == b or g < 2 * a), (a, b, g)
+    for st in STORAGES:
+        for beyond in (0, 1):
+            assert ask(("cover", 128 * 128, st, beyond), ("cover", 73728, st, beyond)) == [[SMALL], [SMALL]]
+            assert ask(("cover", 73729, st, beyond)) == [[STRIPS if beyond and st != mdf.F64 else LARGE]]
