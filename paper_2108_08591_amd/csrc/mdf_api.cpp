@@ -380,9 +380,10 @@ mdf_status advance_case(mdf_ctx *ctx, int k, int64_t nsteps, bool check_last, ui
                         hipStream_t st, int *nblocks)
 {
     if (march_form(ctx)) {
+        const KCase &p = ctx->kc[k];
+        const mdf::Cover cover = mdf::march_emit_cover(ctx->cover, fields);
         while (nsteps > 0) {
-            const KCase &p = ctx->kc[k];
-            const int n = mdf::march_next(nsteps, mdf::march_max(ctx->cover, ctx->storage,
+            const int n = mdf::march_next(nsteps, mdf::march_max(cover, ctx->storage,
                                                                  ctx->bufs[k].links != nullptr, general_case(p)));
             if (n == 1) {
                 nsteps -= 1;
@@ -393,7 +394,7 @@ mdf_status advance_case(mdf_ctx *ctx, int k, int64_t nsteps, bool check_last, ui
             hipError_t e = n == 2 ? mdf::launch_step2(ctx->lattice, ctx->storage, p, ctx->bufs[k], ctx->cur[k], fields,
                                                       out, ctx->shape, st)
                                   : mdf::launch_march(ctx->lattice, ctx->storage, p, ctx->bufs[k], ctx->cur[k], n,
-                                                      ctx->cover, fields, out, ctx->shape, st);
+                                                      cover, fields, out, ctx->shape, st);
             if (e != hipSuccess) return device_error(ctx, e, "launch of several steps");
             ctx->cur[k] ^= 1;
             ctx->time[k] += n;
@@ -480,7 +481,7 @@ mdf_status batch_upload(mdf_ctx *ctx, const std::vector<int> &active, uint32_t f
 {
     const int n = ctx->ncases;
     long long units = 0;                // of all cases, active or not
-    ctx->cover = cover_of(ctx, active);
+    ctx->cover = mdf::march_emit_cover(cover_of(ctx, active), fields);
     ctx->h_tab.resize(n);
     for (int k = 0; k < n; ++k) {
         mdf::BatchEntry &e = ctx->h_tab[k];

@@ -221,6 +221,16 @@ inline Cover march_cover(long long nodes, int storage, bool beyond_cache)
     return storage != MDF_F64 && beyond_cache ? kCoverStrips : kCoverLarge;
 }
 
+// Units of such launches that emit: a strip that accumulates fields reads and
+// writes them at every step of every row and waits each time, a tile takes all
+// its nodes' at once.  21 steps, in strips, tiles and (before) launches of one
+// and two steps: 4096^2 FP16 6.33, 4.51 and 5.57 ms, BF16 6.87, 4.93 and 5.94,
+// 8192^2 FP32 27.6, 24.5 and 30.5.
+inline Cover march_emit_cover(Cover cover, uint32_t fields)
+{
+    return cover == kCoverStrips && (fields & MDF_FIELD_ACCUMULATE) ? kCoverLarge : cover;
+}
+
 // Blocks (or wavefronts, in strips) of a batched launch of several steps whose
 // running cases have `active` units, of `all` in the batch: the next power of
 // two, so that a captured launch serves many sets of running cases.  100 steps

@@ -23,6 +23,9 @@ int main()
         } else if (!std::strcmp(what, "cover")) {       // nodes storage beyond_cache
             if (std::scanf("%d%d%d", a, a + 1, a + 2) != 3) return 1;
             std::printf("%d\n", int(mdf::march_cover(a[0], a[1], a[2] != 0)));
+        } else if (!std::strcmp(what, "emit")) {        // cover fields
+            if (std::scanf("%d%d", a, a + 1) != 2) return 1;
+            std::printf("%d\n", int(mdf::march_emit_cover(mdf::Cover(a[0]), uint32_t(a[1]))));
         } else {
             return 1;
         }

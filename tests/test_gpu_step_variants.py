@@ -165,3 +165,29 @@ def test_units_follow_the_running_cases(storage, sizes):
         assert stats["failed"] == 0 and stats["replayed"] == 2 * len(sets) + 1
     assert all(torch.isfinite(t).all() for t in out[0])
     assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("storage,sizes", [("f32", [(1200, 1100), (64, 64), (1000, 1001)]),
+                                           ("f16dev", [(1700, 1600), (57, 300), (1500, 1300)])])
+def test_accumulation_beyond_the_cache_in_batches(storage, sizes):
+    """Accumulated fields (tiles) between steps and emission (strips) of a batch
+    beyond the Infinity Cache, in chunks of one length."""
+    print(f"[gpu] accumulation batch {storage}", flush=True)
+    stream = torch.cuda.Stream()
+    out = []
+    for form in (0, 2):
+        rng = np.random.default_rng(13)
+        specs = [_spec(nx, ny, k % 2 == 0, True, rng) for k, (nx, ny) in enumerate(sizes)]
+        init = [_init(nx, ny, storage, k) for k, (nx, ny) in enumerate(sizes)]
+        with torch.cuda.stream(stream):
+            s = mdf.Solver(specs, storage=storage, init=("fields", init), u_ref=0.1, stream=stream)
+            s.set_launch(64, 4, 8, form)
+            acc = [torch.zeros_like(t) for t in s.new_field_buffers(MOM)]
+            s.step(9)
+            s.step_emit(9, MOM | mdf.FIELD_ACCUMULATE, acc)
+            s.step(9)
+            s.step_emit(9, MOM | mdf.FIELD_ACCUMULATE, acc)
+            out.append(acc + s.step_emit(9, MOM) + [s.populations(k) for k in range(3)])
+        stream.synchronize()
+    assert all(torch.isfinite(t).all() for t in out[0])
+    assert all(torch.equal(a, b) for a, b in zip(*out))

@@ -71,3 +71,9 @@ def test_units_of_a_batch(ask):
         for beyond in (0, 1):
             assert ask(("cover", 128 * 128, st, beyond), ("cover", 73728, st, beyond)) == [[SMALL], [SMALL]]
             assert ask(("cover", 73729, st, beyond)) == [[STRIPS if beyond and st != mdf.F64 else LARGE]]
+
+
+def test_accumulated_fields_are_not_emitted_from_strips(ask):
+    for cover in (STRIPS, SMALL, LARGE):
+        plain, acc = ask(("emit", cover, mdf.FIELD_ALL), ("emit", cover, mdf.FIELD_VORT | mdf.FIELD_ACCUMULATE))
+        assert plain == [cover] and acc == [LARGE if cover == STRIPS else cover]
