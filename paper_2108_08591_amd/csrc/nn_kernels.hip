@@ -18,6 +18,7 @@
 #include <mutex>
 
 #include "mdfnn.h"
+#include "nn_rules.h"
 
 namespace mdfnn {
 namespace {
@@ -198,8 +199,8 @@ __device__ __forceinline__ void conv_out(const f32x4 &acc, const float *__restri
 // along M, so that a lane ends with four consecutive channels of a pixel,
 // written as 8 bytes.  Rows of the LDS tiles are not padded: their 16-byte
 // chunks are permuted by the row, so that eight consecutive rows' reads of one
-// chunk lie in distinct banks; 24 KB (BN = 64) leave room for six blocks, whose
-// products cover each other's barriers and loads.  Whether a tap of a staged
+// chunk lie in distinct banks; 24 KB and 88 registers (BN = 64) leave room for
+// five blocks, whose products cover each other's barriers and loads.  Whether a tap of a staged
 // pixel lies inside the image is a bit of a mask formed once.  The chunks of a
 // tap follow each other and the taps as in k_conv_fwd_lds: the sums are the
 // same bits.  (K steps of 64 channels, or 64 x 64 products per wave, need fewer
@@ -305,27 +306,27 @@ k_conv_fwd_run(const uint16_t *__restrict__ x1, int c1, const uint16_t *__restri
 }
 
 // The same products for 32 input channels from a two-dimensional pixel tile.
-// Block: 4 waves, 16 x 16 pixels of one image by BN output channels; wave v
-// owns rows [4v, +4) of the tile and all BN channels as (BN / 16) x 4 MFMA
-// blocks, the channels along M, so that a lane ends with four consecutive
-// channels of one pixel.  The block stages the 18 x 18 input pixels around the
-// tile and the weights of all nine taps (BN x 9 x 32) in LDS once and takes
-// the nine taps' products from there: an input value is read from global
-// memory 1.3 times instead of nine times, and one barrier serves 36 BN / 16
-// products per wave.  With one chunk of 32 channels the taps follow each other
+// Block: 4 waves, 16 x 16 pixels of one image by 32 output channels; wave v
+// owns rows [4v, +4) of the tile and all 32 channels as 2 x 4 MFMA blocks, the
+// channels along M, so that a lane ends with four consecutive channels of one
+// pixel.  The block stages the 18 x 18 input pixels around the tile and the
+// weights of all nine taps (32 x 9 x 32) in LDS once and takes the nine taps'
+// products from there: an input value is read from global memory 1.3 times
+// instead of nine times, and one barrier serves 72 products per wave.  With one chunk of 32 channels the taps follow each other
 // as in k_conv_fwd_lds, so the sums are the same bits; with more, taking a
 // chunk's nine taps together would change their order.
 // 16 x 256 x 256 pixels, 32 -> 32 channels: 66 us (130 us in runs of 128 pixels),
-// bound by the latency of a block's only loads, three blocks per CU.
+// bound by the latency of a block's only loads, three blocks per CU.  (64 output
+// channels a block, two blocks per CU: 32 -> 64 channels, 1024 pixels 15.4 and 9.2
+// us, 2^18 pixels 39.0 and 34.9, 2^20 pixels 139 and 116.)
 constexpr int kTlPx = 18 * 18;
 
-template <int BN>
-__global__ void __launch_bounds__(256, BN == 32 ? 3 : 2)
+__global__ void __launch_bounds__(256, 3)
 k_conv_fwd_tile(const uint16_t *__restrict__ x, const uint16_t *__restrict__ w, const float *__restrict__ bias, int H, int W,
                 int gx, int gy, int cout,
                 int relu, const uint16_t *__restrict__ mask, uint16_t *__restrict__ yb, float *__restrict__ yf)
 {
-    constexpr int MB = BN / 16;
+    constexpr int BN = 32, MB = BN / 16;
     constexpr int NA = kTlPx * 4, KA = (NA + 255) / 256;      // 16-byte chunks of input, per thread
     constexpr int NW = 9 * BN * 4, KW = (NW + 255) / 256;     // of weights
     __shared__ uint4 sA4[kTlPx * kCvLd / 8];
@@ -1066,18 +1067,6 @@ using namespace mdfnn;
 
 extern "C" {
 
-// Pixel tiles (k_conv_fwd_tile) where they cover the images with little
-// waste, or are few enough for one round of the chip, whose length then
-// counts and not the padding: 16 x 256 x 256 pixels, 32 -> 32 channels 66 us
-// against 130 in runs of 128 pixels; but 16 x 9 x 1000 (1.8 times padded, 1008
-// tiles) 21 against 19.
-static bool conv_tiles_pay(int B, int H, int W, int cout)
-{
-    const long long tiles = (long long)B * ((H + 15) / 16) * ((W + 15) / 16);
-    const long long blocks = tiles * (cout % 64 == 0 ? cout / 64 : cout / 32);
-    return blocks <= 512 || tiles * 256 * 5 <= 8LL * B * H * W;
-}
-
 int mdfnn_conv3x3_fwd(const uint16_t *x1, int c1, const uint16_t *x2, int c2, const uint16_t *w,
                       const float *bias, int B, int H, int W, int cout, int relu, const uint16_t *mask,
                       uint16_t *y_bf16, float *y_f32, void *stream)
@@ -1088,35 +1077,25 @@ int mdfnn_conv3x3_fwd(const uint16_t *x1, int c1, const uint16_t *x2, int c2, co
     if (M > (1LL << 31)) return MDFNN_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const unsigned gx = (unsigned)((M + kCvBM - 1) / kCvBM);
-    const int tgx = (W + 15) / 16, tgy = (H + 15) / 16;
+    // four channels at a time need aligned outputs; k_conv_fwd_lds writes one
     const bool wide = (reinterpret_cast<uintptr_t>(mask) % 8 == 0) && (reinterpret_cast<uintptr_t>(y_bf16) % 8 == 0) &&
                       (reinterpret_cast<uintptr_t>(y_f32) % 16 == 0);
-    if (wide && c1 + c2 == 32 && conv_tiles_pay(B, H, W, cout)) {
-        const unsigned nt = (unsigned)tgx * tgy * B;
-        if (cout % 64 == 0)
-            hipLaunchKernelGGL(k_conv_fwd_tile<64>, dim3(nt, cout / 64), dim3(256), 0, st, x1, w, bias, H, W,
-                               tgx, tgy, cout, relu, mask, y_bf16, y_f32);
-        else
-            hipLaunchKernelGGL(k_conv_fwd_tile<32>, dim3(nt, cout / 32), dim3(256), 0, st, x1, w, bias, H, W,
-                               tgx, tgy, cout, relu, mask, y_bf16, y_f32);
+    switch (wide ? conv_form(B, H, W, c1 + c2, cout, !y_bf16) : kConvLds) {
+    case kConvTile: {
+        const int tgx = (W + 15) / 16, tgy = (H + 15) / 16;
+        hipLaunchKernelGGL(k_conv_fwd_tile, dim3((unsigned)tgx * tgy * B, cout / 32), dim3(256), 0, st, x1, w, bias, H, W,
+                           tgx, tgy, cout, relu, mask, y_bf16, y_f32);
         return status(hipGetLastError());
     }
-    // Runs in small blocks (k_conv_fwd_run), 32 channels wide where 64 would
-    // leave the chip half empty, and k_conv_fwd_lds where its wider blocks win:
-    // long sums over many blocks of 128 channels, and many blocks of 32
-    // (us, k_conv_fwd_lds / 64 wide / 32 wide: 16 x 128 x 128, 192 -> 64: 156 / 153 /
-    // 293; 16 x 32 x 32, 256 -> 256: 67 / 55 / 58; 1 x 32 x 32, 256 -> 256: 65 / 45 / 36;
-    // 16 x 64 x 64, 384 -> 128: 111 / 119 / 209; 16 x 256 x 256, 96 -> 32: 193 / - / 195).
-    const long long runs = gx;
-    const bool lds = cout % 64 != 0 ? runs * (cout / 32) > 512 : cout % 128 == 0 && c1 + c2 > 256 && runs * (cout / 128) >= 512;
-    if (wide && !lds) {
-        if (cout % 64 == 0 && runs * (cout / 64) > 256)
-            hipLaunchKernelGGL(k_conv_fwd_run<64>, dim3(gx, cout / 64), dim3(256), 0, st, x1, c1, x2, c2, w, bias, B, H, W,
-                               cout, relu, mask, y_bf16, y_f32);
-        else
-            hipLaunchKernelGGL(k_conv_fwd_run<32>, dim3(gx, cout / 32), dim3(256), 0, st, x1, c1, x2, c2, w, bias, B, H, W,
-                               cout, relu, mask, y_bf16, y_f32);
+    case kConvRun32:
+        hipLaunchKernelGGL(k_conv_fwd_run<32>, dim3(gx, cout / 32), dim3(256), 0, st, x1, c1, x2, c2, w, bias, B, H, W,
+                           cout, relu, mask, y_bf16, y_f32);
         return status(hipGetLastError());
+    case kConvRun64:
+        hipLaunchKernelGGL(k_conv_fwd_run<64>, dim3(gx, cout / 64), dim3(256), 0, st, x1, c1, x2, c2, w, bias, B, H, W,
+                           cout, relu, mask, y_bf16, y_f32);
+        return status(hipGetLastError());
+    default: break;
     }
     if (cout % 128 == 0)
         hipLaunchKernelGGL(k_conv_fwd_lds<128>, dim3(gx, cout / 128), dim3(256), 0, st, x1, c1, x2, c2, w, bias, B, H,

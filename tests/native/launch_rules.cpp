@@ -1,10 +1,11 @@
-// launch_rules.cpp -- prints what the launch rules of mdf_internal.h choose, for
-// the questions on standard input, one a line.  Built and driven by
+// launch_rules.cpp -- prints what the launch rules of mdf_internal.h and
+// nn_rules.h choose, for the questions on standard input, one a line.  Built and driven by
 // tests/test_launch_rules_cpu.py; no call reaches the device.
 #include <cstdio>
 #include <cstring>
 
 #include "mdf_internal.h"
+#include "nn_rules.h"
 
 int main()
 {
@@ -26,6 +27,13 @@ int main()
         } else if (!std::strcmp(what, "emit")) {        // cover fields
             if (std::scanf("%d%d", a, a + 1) != 2) return 1;
             std::printf("%d\n", int(mdf::march_emit_cover(mdf::Cover(a[0]), uint32_t(a[1]))));
+        } else if (!std::strcmp(what, "plan")) {        // storage sets q nx ny nz
+            if (std::scanf("%d%d%d%d%d%d", a, a + 1, a + 2, a + 3, a + 4, a + 5) != 6) return 1;
+            const mdf::Step2zPlan p = mdf::step2z_plan(a[0], a[1], a[2], a[3], a[4], a[5]);
+            std::printf("%d %.4f\n", p.zc, p.fill);
+        } else if (!std::strcmp(what, "conv")) {        // B H W cin cout f32
+            if (std::scanf("%d%d%d%d%d%d", a, a + 1, a + 2, a + 3, a + 4, a + 5) != 6) return 1;
+            std::printf("%d\n", int(mdfnn::conv_form(a[0], a[1], a[2], a[3], a[4], a[5] != 0)));
         } else {
             return 1;
         }

@@ -1,5 +1,6 @@
-"""The rules that choose launches of several steps (mdf_internal.h), asked on
-the CPU through a small program built from that header."""
+"""The rules that choose launches of several steps (mdf_internal.h) and the
+kernel of a convolution (nn_rules.h), asked on the CPU through a small program
+built from those headers."""
 import os
 import shutil
 import subprocess
@@ -77,3 +78,27 @@ def test_accumulated_fields_are_not_emitted_from_strips(ask):
     for cover in (STRIPS, SMALL, LARGE):
         plain, acc = ask(("emit", cover, mdf.FIELD_ALL), ("emit", cover, mdf.FIELD_VORT | mdf.FIELD_ACCUMULATE))
         assert plain == [cover] and acc == [LARGE if cover == STRIPS else cover]
+
+
+TILE, RUN32, RUN64, LDS = 0, 1, 2, 3
+
+
+def test_kernel_of_a_convolution(ask):
+    """Either side of every line, and sizes whose fastest kernel is known by a
+    wide margin (times in nn_rules.h)."""
+    known = [((8, 512, 64, 256, 128), LDS), ((3, 512, 64, 192, 128), LDS), ((8, 512, 64, 128, 128), LDS),
+             ((16, 64, 64, 384, 128), LDS), ((16, 32, 32, 256, 256), RUN64), ((1, 32, 32, 256, 256), RUN32),
+             ((16, 64, 64, 64, 256), RUN64), ((1, 1024, 64, 512, 64), LDS), ((16, 128, 128, 192, 64), LDS),
+             ((16, 64, 64, 128, 64), RUN64), ((16, 256, 256, 96, 32), LDS), ((1, 32, 32, 64, 64), RUN32),
+             ((16, 256, 256, 32, 32), TILE), ((16, 128, 128, 32, 64), TILE), ((1, 8, 8, 32, 256), TILE)]
+    f32 = [(128, 128, 511, RUN64, LDS), (384, 128, 383, RUN64, LDS), (64, 128, 639, RUN64, LDS), (64, 64, 1280, RUN64, LDS)]
+    lines = [(128, 128, 639, RUN64, LDS), (256, 128, 639, RUN64, LDS), (288, 128, 511, RUN64, LDS),
+             (64, 128, 639, RUN64, LDS), (64, 128, 768, LDS, RUN64), (64, 128, 1152, RUN64, LDS),
+             (128, 128, 192, RUN32, RUN64), (64, 64, 1280, RUN64, LDS), (224, 64, 511, RUN64, LDS),
+             (64, 64, 384, RUN32, RUN64), (64, 32, 1024, RUN32, LDS)]
+    qs = [("conv",) + k + (0,) for k, _ in known]
+    for k, (cin, cout, runs, _, _) in enumerate(lines + f32):
+        qs += [("conv", 1, runs + more, 128, cin, cout, k >= len(lines)) for more in (0, 1)]
+    want = [w for _, w in known] + [w for line in lines + f32 for w in line[3:]]
+    got = [int(v[0]) for v in ask(*qs)]
+    assert got == want, [(q, g, w) for q, g, w in zip(qs, got, want) if g != w]
