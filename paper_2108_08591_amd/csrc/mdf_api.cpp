@@ -48,18 +48,9 @@ int lat_q(int lattice)
 }
 // stored distribution sets: all d + 1, or the d velocity sets (the *_V lattices)
 int lat_ns(int lattice) { return (lattice & 2) ? lat_d(lattice) : lat_d(lattice) + 1; }
-// the default form: several steps per launch on the axis-link lattices.  In 3D
-// two steps per launch pay where the launch is well filled: small grids, and
-// tiles with much padding, leave the chip idle while blocks walk their planes,
-// and walls cost the second step more than the one-step kernel.  Over 51 grids
-// of 24^3 to 256^3 nodes, FP64 and FP32, three and four sets, one step per
-// launch is faster below these lines and two above, but for a few grids close
-// to them (per step, two and one: 64^3 periodic, filled 0.40, 20 and 18 us in
-// FP64; 138 x 148 x 60 periodic, three sets, 0.69, 65 and 88; walls, FP64, four
-// sets: 130 x 97 x 75, 0.69, 103 and 90; 150 x 65 x 150, 0.83, 141 and 160; FP32:
-// 130 x 97 x 75, 0.64, 44 and 40; 138 x 148 x 60, 0.67, 60 and 61).  The 16-bit
-// formats run one step per launch at every size (256^3 346 and 331 us, 64^3 36
-// and 8).
+// the default form: several steps per launch on the axis-link lattices, in 3D
+// where step2z_pays() says so; the 16-bit formats run one step per launch there
+// at every size (256^3 346 and 331 us, 64^3 36 and 8)
 bool lat_fused_default(int lattice, int storage, const mdf_case &c)
 {
     if (lat_diag(lattice)) return false;
@@ -67,9 +58,7 @@ bool lat_fused_default(int lattice, int storage, const mdf_case &c)
     if (storage != MDF_F64 && storage != MDF_F32) return false;
     bool walls = false;
     for (int f = 0; f < 6; ++f) walls = walls || c.bc[f] == MDF_WALL;
-    const int sets = lat_ns(lattice);
-    const double line = !walls ? 0.5 : storage == MDF_F64 && sets == 4 ? 0.72 : 0.64;
-    return mdf::step2z_plan(storage, sets, lat_q(lattice), c.nx, c.ny, c.nz).fill >= line;
+    return mdf::step2z_pays(storage, lat_ns(lattice), lat_q(lattice), walls, c.nx, c.ny, c.nz);
 }
 // population planes of one buffer: every stored set has q directions, but for
 // the set a = 0 of a lattice per set, which has 2d + 1

@@ -309,4 +309,24 @@ inline Step2zPlan step2z_plan(int storage, int sets, int q, int nx, int ny, int 
     return {zc, double(nx) * ny * nz / (double(least) * resident * ni)};
 }
 
+// Two steps per launch pay in 3D where the launch is well filled: small grids,
+// and tiles with much padding, leave the chip idle while blocks walk their
+// planes, and walls cost the second step more than the one-step kernel.  Over 52
+// grids of 24^3 to 256^3 nodes, FP64 and FP32, three and four sets, periodic and
+// between walls, one step per launch is faster below these lines and two above,
+// but for a few grids close to them and the cube of 64 (us per step of two and
+// one; FP64 periodic, four sets: 40 x 40 x 250, filled 0.51, 35.6 and 27.4; 72 x 88 x
+// 120, 0.58, 75.8 and 79.2; 64^3, 0.67, 19.6 and 17.2; three sets: 138 x 148 x 60,
+// 0.73, 60.4 and 88.1; walls, four sets: 130 x 97 x 75, 0.69, 103 and 90; 150 x 65 x
+// 150, 0.83, 143 and 168; FP32 periodic, three sets: 80^3, 0.43, 16.3 and 15.2; 39 x
+// 223 x 123, 0.45, 42.2 and 52.8; walls: 138 x 148 x 60, 0.62, 31.2 and 36.2; four
+// sets: 130 x 97 x 75, 0.56, 44.0 and 40.0; 138 x 148 x 60, 0.67, 59.7 and 60.8).
+inline bool step2z_pays(int storage, int sets, int q, bool walls, int nx, int ny, int nz)
+{
+    double line = walls ? 0.64 : 0.5;
+    if (storage == MDF_F64 && sets == 4) line = walls ? 0.72 : 0.53;
+    if (storage == MDF_F32 && sets == 3) line = 0.44;
+    return step2z_plan(storage, sets, q, nx, ny, nz).fill >= line;
+}
+
 }  // namespace mdf

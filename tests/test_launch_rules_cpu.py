@@ -102,3 +102,18 @@ def test_kernel_of_a_convolution(ask):
     want = [w for _, w in known] + [w for line in lines + f32 for w in line[3:]]
     got = [int(v[0]) for v in ask(*qs)]
     assert got == want, [(q, g, w) for q, g, w in zip(qs, got, want) if g != w]
+
+
+def test_default_form_in_3d(ask):
+    """The grids that the rule's comment cites: their fill as the plan gives it
+    and the form it chooses, which is the faster one but for the 64^3 cube."""
+    cited = [(mdf.F64, 4, 0, (40, 40, 250), 0.51, 0), (mdf.F64, 4, 0, (72, 88, 120), 0.58, 1),
+             (mdf.F64, 4, 0, (64, 64, 64), 0.67, 1), (mdf.F64, 3, 0, (138, 148, 60), 0.73, 1),
+             (mdf.F64, 4, 1, (130, 97, 75), 0.69, 0), (mdf.F64, 4, 1, (150, 65, 150), 0.83, 1),
+             (mdf.F32, 3, 0, (80, 80, 80), 0.43, 0), (mdf.F32, 3, 0, (39, 223, 123), 0.45, 1),
+             (mdf.F32, 3, 1, (138, 148, 60), 0.62, 1), (mdf.F32, 4, 1, (130, 97, 75), 0.56, 0),
+             (mdf.F32, 4, 1, (138, 148, 60), 0.67, 1), (mdf.F32, 4, 0, (256, 256, 256), 0.94, 1)]
+    plans = ask(*[("plan", st, sets, 7) + dims for st, sets, _, dims, _, _ in cited])
+    pays = ask(*[("pays", st, sets, 7, w) + dims for st, sets, w, dims, _, _ in cited])
+    for (st, sets, w, dims, fill, two), (zc, f), (p,) in zip(cited, plans, pays):
+        assert round(f, 2) == fill and p == two, (st, sets, w, dims, zc, f, p)
