@@ -191,3 +191,65 @@ def test_accumulation_beyond_the_cache_in_batches(storage, sizes):
         stream.synchronize()
     assert all(torch.isfinite(t).all() for t in out[0])
     assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("storage,nx,ny,longest", [("f64", 70, 45, 4), ("f64", 300, 259, 4), ("f32", 70, 45, 4),
+                                                   ("f32", 300, 259, 4), ("f32", 1500, 1520, 5), ("f16dev", 70, 45, 4),
+                                                   ("f16dev", 300, 259, 4), ("f16dev", 2100, 2201, 4),
+                                                   ("bf16dev", 2100, 2201, 4)])
+@pytest.mark.parametrize("mask", [False, True])
+@pytest.mark.parametrize("walls", [False, True])
+def test_every_length_of_launch(storage, nx, ny, longest, mask, walls):
+    """Calls of K + 1 steps, one launch of K and one of one (five only without a
+    mask: with one, three and two), plain, emitting and accumulating."""
+    print(f"[gpu] every length {storage} {nx}x{ny} mask={mask} walls={walls}", flush=True)
+    out = []
+    for form in (0, 2):
+        rng = np.random.default_rng(nx)
+        data = _init(nx, ny, storage)
+        solid = (rng.random((ny, nx)) < 0.05).astype(np.uint8) if mask else None
+        if mask:
+            data[:, torch.as_tensor(solid).bool()] = 0.0
+        s = mdf.Solver(_spec(nx, ny, walls, walls, rng), storage=storage, solid=[solid] if mask else None,
+                       init=("fields", [data]), u_ref=0.1)
+        s.set_launch(64, 4, 8, form)
+        got = []
+        for k in range(2, longest + 1):
+            s.step(k + 1)
+            got += [s.moments()] + s.step_emit(k + 1, MOM)
+            acc = [torch.zeros_like(t) for t in s.new_field_buffers(MOM)]
+            s.step_emit(k + 1, MOM | mdf.FIELD_ACCUMULATE, acc)
+            got += acc
+        out.append(got + [s.populations()])
+    assert all(torch.isfinite(t).all() for t in out[0])
+    assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("storage,sizes,n", [("f32", [(1200, 1100), (64, 64), (1000, 1001)], 6),
+                                             ("f32", [(1200, 1100), (64, 64), (1000, 1001)], 11),
+                                             ("f16dev", [(1700, 1600), (57, 300), (1500, 1300)], 5)])
+@pytest.mark.parametrize("mask", [False, True])
+def test_longest_launches_in_batches(storage, sizes, n, mask):
+    """Strips of a batch at their longest launch, plain and emitting."""
+    print(f"[gpu] longest launches batch {storage} n={n} mask={mask}", flush=True)
+    stream = torch.cuda.Stream()
+    out = []
+    for form in (0, 2):
+        rng = np.random.default_rng(17)
+        specs = [_spec(nx, ny, k % 2 == 0, True, rng) for k, (nx, ny) in enumerate(sizes)]
+        init = [_init(nx, ny, storage, k) for k, (nx, ny) in enumerate(sizes)]
+        solid = None
+        if mask:
+            solid = [(rng.random((ny, nx)) < 0.05).astype(np.uint8) if k != 1 else None
+                     for k, (nx, ny) in enumerate(sizes)]
+            for t, m in zip(init, solid):
+                if m is not None:
+                    t[:, torch.as_tensor(m).bool()] = 0.0
+        with torch.cuda.stream(stream):
+            s = mdf.Solver(specs, storage=storage, solid=solid, init=("fields", init), u_ref=0.1, stream=stream)
+            s.set_launch(64, 4, 8, form)
+            s.step(n)
+            out.append([s.populations(k) for k in range(3)] + s.step_emit(n, MOM) + [s.populations(0)])
+        stream.synchronize()
+    assert all(torch.isfinite(t).all() for t in out[0])
+    assert all(torch.equal(a, b) for a, b in zip(*out))
