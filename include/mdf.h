@@ -210,18 +210,19 @@ mdf_status mdf_init(mdf_ctx **out, mdf_lattice lattice, mdf_storage storage,
 
 /* Advance every case by nsteps time steps of eq. 3-21 (fused pull
  * streaming, wall rule, moments, equilibrium, MRT collision and forcing).
- * A context of several cases advances all of them in one persistent launch
- * per step over the flattened (case, tile) list; K-step chunks on a
- * non-null stream are captured once as a HIP graph and replayed.  The
+ * A context of several cases advances all of them in launches over the
+ * flattened (case, tile) list; K-step chunks on a non-null stream are captured
+ * as a HIP graph and replayed.  The
  * results are bitwise those of one context per case with the same launch
  * shape. */
 mdf_status mdf_step(mdf_ctx *ctx, int32_t nsteps, void *stream);
 
-/* As mdf_step, and every step also writes the selected fields (MDF_FIELD_*)
- * at the new time into out[case] (channel-major, compute dtype, overwritten
- * each step: on return they hold the fields at the final time; with
- * MDF_FIELD_ACCUMULATE every step adds them instead).  MDF_EINVAL for
- * unknown bits or no field selected. */
+/* As mdf_step, and the selected fields (MDF_FIELD_*) are written into
+ * out[case] (channel-major, compute dtype): on return they hold the fields at
+ * the final time.  What they hold in between is not specified: every launch
+ * writes them at its last step, so with several steps per launch the steps
+ * before it leave none.  With MDF_FIELD_ACCUMULATE every step adds its fields
+ * instead.  MDF_EINVAL for unknown bits or no field selected. */
 mdf_status mdf_step_emit(mdf_ctx *ctx, int32_t nsteps, uint32_t fields, void *const *out,
                          void *stream);
 
@@ -250,8 +251,7 @@ mdf_status mdf_check(mdf_ctx *ctx, double *res, int32_t *status, void *stream);
 /* Run until every case reaches res < tol (the residual of mdf_check,
  * evaluated every K steps inside the last step of each K-step chunk), goes
  * non-finite, or max_steps steps were taken.  Waits for the device once per
- * chunk.  fields/out: as mdf_step_emit (every step writes the selected
- * fields), or 0/NULL.  case_status (host, ncases or NULL): 0 converged,
+ * chunk.  fields/out: as mdf_step_emit, or 0/NULL.  case_status (host, ncases or NULL): 0 converged,
  * 1 non-finite, 2 not converged, 3 disabled (mdf_set_active).  steps_taken/final_res: host arrays of
  * ncases or NULL.  Cases that converge stop advancing; the others continue.
  * Returns MDF_EUNSTABLE if any case went non-finite. */
@@ -274,17 +274,20 @@ mdf_status mdf_invariants(const mdf_ctx *ctx, int32_t case_id, double *out, void
  *      for MDF_STORAGE_F64, 4 for the other storages), read and written as one
  *      16-byte (8-byte for the 16-bit storages) access per plane;
  *   2  several steps per launch (the lattices with axis links only: D2Q5,
- *      D2Q4, D3Q7, D3Q6 and their *_V forms).  2D: three or four steps (five in
- *      FP32 beyond the Infinity Cache).  FP64 grids and grids inside the
- *      cache work in tiles that take all steps with a halo of 4 nodes; FP32
- *      and 16-bit grids beyond it in strips of columns, walked row by row.
+ *      D2Q4, D3Q7, D3Q6 and their *_V forms).  2D: two to four steps (five in
+ *      FP32 beyond the Infinity Cache without obstacles, force field and
+ *      Scheme II).  FP64 grids, grids inside the cache and accumulated fields
+ *      work in tiles that take all steps with a halo of 4 nodes; FP32 and
+ *      16-bit grids beyond it in strips of columns, walked row by row; two
+ *      steps in tiles of 64 x 4/8 nodes (FP64/other storages).
  *      3D: two steps; tiles of 32 x 4 (FP64), 32 x 8 (FP32) or 64 x 8 (16-bit)
  *      nodes walk a chunk of z-planes, keeping the intermediate state of
  *      three planes in LDS.  Either way the state crosses HBM once per
  *      launch.  mdf_step, mdf_step_emit and mdf_run_steady run their steps this
  *      way but for the last one of each call (and of each K-step chunk), and
- *      one or two before it that make no such launch, which are of form 0
- *      with these bx, by; batched 3D contexts run every step as form 0.
+ *      one before it in a call of two and, in 3D, in calls of an even number,
+ *      which are of form 0 with these bx, by; batched 3D contexts run every
+ *      step as form 0.
  * The read kernels always use one node per thread.  Default 64 x 4, 8
  * groups, form 2 on the axis-link lattices (in 3D with FP64 and FP32
  * storage, on grids that fill its launch well: from about a million nodes,
@@ -341,7 +344,8 @@ mdf_status mdf_set_active(mdf_ctx *ctx, const int32_t *active);
  * 64x4, 128x2, 128x1 without; for lattices with axis links also several
  * steps per launch with and without bands) on `trial_steps` real steps each and
  * keeping the
- * fastest.  Every case advances by (trial_steps + 1) steps per candidate
+ * fastest.  Fewer than three trial steps run as single steps in every form;
+ * several steps per launch are timed as they run from about ten.  Every case advances by (trial_steps + 1) steps per candidate
  * tried (results are bitwise independent of the shape).  chosen: host
  * int[4] (bx, by, groups, form) or NULL; best_ms: host double, time per
  * step, or NULL.  Waits for the device. */

@@ -37,8 +37,8 @@ bool lat_ok(int lattice) { return (lattice >= MDF_D2Q5 && lattice <= MDF_D3Q15_V
 bool lat_2d(int lattice) { return (lattice & 1) == 0; }
 bool lat_restfree(int lattice) { return (lattice & 4) != 0 && !lat_mixed(lattice); }
 bool lat_diag(int lattice) { return (lattice & 8) != 0; }
-// two steps per launch: lattices with axis links (2D tiles, or 3D tiles
-// walking z-planes)
+// several steps per launch: lattices with axis links (2D tiles and strips of
+// columns; two steps in 3D, tiles walking z-planes)
 bool lat_fusable(int lattice) { return !lat_diag(lattice); }
 int lat_d(int lattice) { return lat_2d(lattice) ? 2 : 3; }
 int lat_q(int lattice)
@@ -823,7 +823,7 @@ mdf_status mdf_set_launch(mdf_ctx *ctx, int32_t bx, int32_t by, int32_t groups, 
     if (groups < 0 || groups > 64) return fail(ctx, MDF_EINVAL, "mdf_set_launch: groups outside [0, 64]");
     if (form < 0 || form > 2) return fail(ctx, MDF_EINVAL, "mdf_set_launch: form must be 0, 1 or 2");
     if (form == 2 && !lat_fusable(ctx->lattice))
-        return fail(ctx, MDF_EINVAL, "mdf_set_launch: two steps per launch needs a lattice with axis links");
+        return fail(ctx, MDF_EINVAL, "mdf_set_launch: several steps per launch needs a lattice with axis links");
     if (form == 1 && lat_diag(ctx->lattice))
         return fail(ctx, MDF_EINVAL, "mdf_set_launch: the vector form needs a lattice with axis links");
     ctx->shape = LaunchShape{bx, by, groups, form == 1 ? 2 : 1, form == 2 ? 1 : 0};
@@ -1084,7 +1084,7 @@ mdf_status mdf_autotune(mdf_ctx *ctx, int32_t trial_steps, int32_t *chosen, doub
     int bi = 0;
     mdf_status r = MDF_OK;
     for (int c = 0; c < int(sizeof cand / sizeof cand[0]) && r == MDF_OK; ++c) {
-        // two steps per launch: lattices with axis links
+        // several steps per launch: lattices with axis links
         if (cand[c][3] == 2 && !lat_fusable(ctx->lattice)) continue;
         if (cand[c][3] == 1 && lat_diag(ctx->lattice)) continue;
         r = mdf_set_launch(ctx, cand[c][0], cand[c][1], cand[c][2], cand[c][3]);

@@ -213,11 +213,15 @@ int read_blocks(const KCase &p, LaunchShape shape);
 // the traffic per step counts (4096^2: FP32 116 us per step in strips and 166
 // in tiles, FP16 99 and 125); tiles inside it (1024^2: FP32 9.8 and 7.5 us,
 // FP16 13.9 and 9.4) and for FP64 (4096^2 320 and 247 us, 1024^2 21.5 and
-// 13.4), small ones up to 73728 nodes (256^2: FP64 2.5 us per step in small and
-// 2.6 in large ones, FP32 1.7 and 1.9; 384^2: 4.0 and 3.1, 2.8 and 2.0).
+// 13.4), small ones up to 73728 nodes, 65536 in the 16-bit formats (101 steps, us
+// in small and in large ones: 256^2 FP64 226 and 258, FP32 162 and 183, FP16 199 and
+// 197; 264^2 237 and 262, 175 and 185, 227 and 204; 288^2 265 and 266, 191 and 184,
+// 246 and 197; 320^2 293 and 282, 208 and 194, 273 and 200; batches as their nodes:
+// 4 x 128^2 257 and 292, 194 and 207, 233 and 231; 6 x 128^2 329 and 312, 234 and 223,
+// 291 and 244).
 inline Cover march_cover(long long nodes, int storage, bool beyond_cache)
 {
-    if (nodes <= 73728) return kCoverSmall;
+    if (nodes <= (storage == MDF_F64 || storage == MDF_F32 ? 73728 : 65536)) return kCoverSmall;
     return storage != MDF_F64 && beyond_cache ? kCoverStrips : kCoverLarge;
 }
 

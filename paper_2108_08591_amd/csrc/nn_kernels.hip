@@ -11,7 +11,8 @@
 // Activations are NHWC, so one K step of 32 of the forward product (one
 // tap, 32 consecutive channels) is one 16-byte chunk per pixel and weight
 // row, staged through LDS as [row][32 channels]; the weight gradient, whose
-// K steps are 32 pixels, stages its tiles transposed ([channel][pixel]).
+// K steps are 32 pixels, stages its tiles as they lie in memory and transposes
+// them as it reads them from LDS.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -52,7 +53,7 @@ __device__ __forceinline__ bf16x8 zero8()
 
 // LDS-staged implicit GEMM for the forward and data-gradient products, in
 // runs of 128 pixels that ignore the image's rows: where its wide blocks pay
-// (mdfnn_conv3x3_fwd), and for outputs not aligned to 8 bytes.
+// (nn_rules.h), and for outputs not aligned to 8 bytes.
 // Block: 4 waves, a 128-pixel x BN-channel output tile; wave (wm, wn) owns
 // pixels [64 wm, +64) and channels [wn BN/2, +BN/2) as 4 x (BN/32) MFMA
 // blocks of 16 x 16.  Each K step (one tap, 32 input channels) stages the

@@ -70,8 +70,9 @@ def test_units_of_a_batch(ask):
         assert a <= g <= b and (g == b or g < 2 * a), (a, b, g)
     for st in STORAGES:
         for beyond in (0, 1):
-            assert ask(("cover", 128 * 128, st, beyond), ("cover", 73728, st, beyond)) == [[SMALL], [SMALL]]
-            assert ask(("cover", 73729, st, beyond)) == [[STRIPS if beyond and st != mdf.F64 else LARGE]]
+            most = 73728 if st in (mdf.F64, mdf.F32) else 65536
+            assert ask(("cover", 128 * 128, st, beyond), ("cover", most, st, beyond)) == [[SMALL], [SMALL]]
+            assert ask(("cover", most + 1, st, beyond)) == [[STRIPS if beyond and st != mdf.F64 else LARGE]]
 
 
 def test_accumulated_fields_are_not_emitted_from_strips(ask):
