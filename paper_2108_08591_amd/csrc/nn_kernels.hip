@@ -1081,7 +1081,7 @@ int mdfnn_conv3x3_fwd(const uint16_t *x1, int c1, const uint16_t *x2, int c2, co
     // four channels at a time need aligned outputs; k_conv_fwd_lds writes one
     const bool wide = (reinterpret_cast<uintptr_t>(mask) % 8 == 0) && (reinterpret_cast<uintptr_t>(y_bf16) % 8 == 0) &&
                       (reinterpret_cast<uintptr_t>(y_f32) % 16 == 0);
-    switch (wide ? conv_form(B, H, W, c1 + c2, cout, !y_bf16) : kConvLds) {
+    switch (wide ? conv_form(B, H, W, c1 + c2, cout, {bias != nullptr, mask != nullptr, !y_bf16}) : kConvLds) {
     case kConvTile: {
         const int tgx = (W + 15) / 16, tgy = (H + 15) / 16;
         hipLaunchKernelGGL(k_conv_fwd_tile, dim3((unsigned)tgx * tgy * B, cout / 32), dim3(256), 0, st, x1, w, bias, H, W,

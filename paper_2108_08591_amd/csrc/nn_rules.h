@@ -20,37 +20,51 @@ inline bool conv_tiles_pay(int B, int H, int W, int cout)
     return tiles * (cout / 32) <= 512 || tiles * 256 * 5 <= 8LL * B * H * W;
 }
 
+// What a call asks of the outputs: a bias, the mask of a data gradient, FP32
+// alone.
+struct ConvOuts {
+    bool bias, mask, f32;
+};
+
 // Runs in small blocks, 32 channels wide where 64 would leave the chip half
-// empty, and k_conv_fwd_lds where its wider blocks fill it.  Resident are 768
-// blocks of 128 channels (three per CU), 1280 of k_conv_fwd_run<64> (five).
-// Every output width from 32 to 384, 64 to 768 input channels, 64 to 2^20
-// pixels (us, k_conv_fwd_lds / 64 wide / 32 wide):
-//   128 outputs and multiples: 256 inputs, 2^18 pixels 255 / 391 / 794, 98304
-//   100 / 147 / 245, 65536 78 / 80 / 121; 128 inputs, 2^18 pixels 148 / 187 / 353;
-//   384 inputs, 65536 pixels 111 / 119 / 209; 256 -> 256 inputs, 16384 pixels 67 /
-//   55 / 58, 1024 pixels 65 / 45 / 36.  Short sums lose more by a last round that
-//   is nearly empty than they gain by width: 64 -> 256, 65536 pixels (1024 blocks)
-//   1.29 times 64 wide.
-//   FP32 outputs alone, which k_conv_fwd_lds writes faster than BF16: 128 inputs,
-//   65536 pixels 38 and 41, 384 inputs, 50176 pixels 97 and 107.
-//   64 and odd multiples: 512 inputs, 65536 pixels 120 / 144 / 139, 192 inputs, 2^18
-//   pixels 149 / 156 / 290; 128 inputs, 65536 pixels 6 % slower than 64 wide.
-//   32 and odd multiples: 96 inputs, 2^20 pixels 193 / - / 195; below 1024 blocks
-//   k_conv_fwd_run is up to 1.4 times as fast.
-inline ConvForm conv_form(int B, int H, int W, int cin, int cout, bool f32)
+// empty, and k_conv_fwd_lds where its wider blocks win: in rounds of resident
+// blocks (768 of 128 channels, three per CU; 1280 of k_conv_fwd_run<64>, five),
+// in many blocks, or in long sums.  It writes one channel at a time: a mask, and a
+// bias under short sums, cost it more.  Every output width of 32 to 384, 32 to 768
+// inputs, 2^10 to 2^20 pixels (us, k_conv_fwd_lds / 64 wide / 32 wide, with bias and
+// with a mask):
+//   128 outputs, 256 inputs, 2^18 pixels 274 / 392 / 790 and 283 / 390 / 824, 98304 (one
+//   round and two) 104 / 153 / 244 and 106 / 150 / 254, 65536 79 / 81 / 123 and 80 / 81 /
+//   127; 128 inputs, 131072 pixels 92 / 93 / 149 and 96 / 92 / 166; 64 inputs, 2^18
+//   pixels 109 / 102 / 128 and 115 / 99 / 145; 384 inputs, 65536 pixels 111 / 125 / 212
+//   and 112 / 126 / 216; 256 outputs, 256 inputs, 16384 pixels 67 / 55 / 58 and 68 / 53 /
+//   58; without bias, 384 inputs, 16 x 56 x 56 pixels 99 / 107; FP32 alone without bias,
+//   128 inputs, 65536 pixels 38 / 41, 64 -> 64, 2^18 pixels 48 / 51.
+//   64 outputs, 192 inputs, 2^18 pixels 150 / 157 / 289 and 156 / 157 / 304; 64 inputs 57 /
+//   57 / 67 and 65 / 54 / 73; 512 inputs, 65536 pixels 120 / 143 / 140 and 123 / 142 / 141.
+//   32 outputs, 96 inputs (64 + 32), 2^18 pixels 62 / - / 67 and 65 / - / 68; 128 inputs,
+//   2^20 pixels 329 / - / 353 and 350 / - / 403, 131072 pixels 42 / - / 37 and 44 / - /
+//   37.
+inline ConvForm conv_form(int B, int H, int W, int cin, int cout, ConvOuts o)
 {
     if (cin == 32 && conv_tiles_pay(B, H, W, cout)) return kConvTile;
     const long long runs = ((long long)B * H * W + 127) / 128;
-    if (cout % 64 != 0) return runs * (cout / 32) > 1024 ? kConvLds : kConvRun32;
-    const long long narrow = runs * (cout / 64);
+    if (cout % 64 != 0) return cin >= 96 && runs * (cout / 32) >= 2048 ? kConvLds : kConvRun32;
+    const long long narrow = runs * (cout / 64), blocks = narrow / 2;
     bool lds;
     if (cout % 128 == 0) {
-        const long long blocks = runs * (cout / 128), rounds = (blocks + 767) / 768;
-        const bool filled = 4 * blocks > 3 * 768 * rounds;
-        const int least = !f32 || cin < 128 ? (cin > 256 ? 512 : 640) : (cin > 256 ? 384 : 512);
-        lds = blocks >= least && (cin >= 128 || filled);
+        const bool fewer = (blocks + 767) / 768 < (narrow + 1279) / 1280;
+        if (cin < 96) {
+            lds = fewer && !o.mask && (blocks <= 768 || !o.bias);
+        } else {
+            long long least = 1280;
+            if (cin >= 192) least = o.mask && cin < 256 ? 1024 : 640;
+            if (cin > 256 || (cin >= 128 && !o.bias && !o.mask)) least = 512;
+            if (cin > 256 && !o.bias && !o.mask) least = 384;
+            lds = fewer || blocks >= least;
+        }
     } else {
-        lds = narrow > 1280 || (cin >= 224 && narrow >= 512);
+        lds = ((cin >= 128 || (o.f32 && !o.bias)) && !o.mask && narrow > 1280) || (cin >= 288 && narrow > 384 && narrow <= 512);
     }
     return lds ? kConvLds : narrow > 384 ? kConvRun64 : kConvRun32;
 }

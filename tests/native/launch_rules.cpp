@@ -34,9 +34,10 @@ int main()
         } else if (!std::strcmp(what, "pays")) {        // storage sets q walls nx ny nz
             if (std::scanf("%d%d%d%d%d%d%d", a, a + 1, a + 2, a + 3, a + 4, a + 5, a + 6) != 7) return 1;
             std::printf("%d\n", int(mdf::step2z_pays(a[0], a[1], a[2], a[3] != 0, a[4], a[5], a[6])));
-        } else if (!std::strcmp(what, "conv")) {        // B H W cin cout f32
-            if (std::scanf("%d%d%d%d%d%d", a, a + 1, a + 2, a + 3, a + 4, a + 5) != 6) return 1;
-            std::printf("%d\n", int(mdfnn::conv_form(a[0], a[1], a[2], a[3], a[4], a[5] != 0)));
+        } else if (!std::strcmp(what, "conv")) {        // B H W cin cout bias mask f32
+            if (std::scanf("%d%d%d%d%d%d%d%d", a, a + 1, a + 2, a + 3, a + 4, a + 5, a + 6, a + 7) != 8) return 1;
+            std::printf("%d\n", int(mdfnn::conv_form(a[0], a[1], a[2], a[3], a[4],
+                                                         {a[5] != 0, a[6] != 0, a[7] != 0})));
         } else {
             return 1;
         }

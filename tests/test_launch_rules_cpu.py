@@ -85,22 +85,28 @@ TILE, RUN32, RUN64, LDS = 0, 1, 2, 3
 
 
 def test_kernel_of_a_convolution(ask):
-    """Either side of every line, and sizes whose fastest kernel is known by a
-    wide margin (times in nn_rules.h)."""
-    known = [((8, 512, 64, 256, 128), LDS), ((3, 512, 64, 192, 128), LDS), ((8, 512, 64, 128, 128), LDS),
-             ((16, 64, 64, 384, 128), LDS), ((16, 32, 32, 256, 256), RUN64), ((1, 32, 32, 256, 256), RUN32),
-             ((16, 64, 64, 64, 256), RUN64), ((1, 1024, 64, 512, 64), LDS), ((16, 128, 128, 192, 64), LDS),
-             ((16, 64, 64, 128, 64), RUN64), ((16, 256, 256, 96, 32), LDS), ((1, 32, 32, 64, 64), RUN32),
-             ((16, 256, 256, 32, 32), TILE), ((16, 128, 128, 32, 64), TILE), ((1, 8, 8, 32, 256), TILE)]
-    f32 = [(128, 128, 511, RUN64, LDS), (384, 128, 383, RUN64, LDS), (64, 128, 639, RUN64, LDS), (64, 64, 1280, RUN64, LDS)]
-    lines = [(128, 128, 639, RUN64, LDS), (256, 128, 639, RUN64, LDS), (288, 128, 511, RUN64, LDS),
-             (64, 128, 639, RUN64, LDS), (64, 128, 768, LDS, RUN64), (64, 128, 1152, RUN64, LDS),
-             (128, 128, 192, RUN32, RUN64), (64, 64, 1280, RUN64, LDS), (224, 64, 511, RUN64, LDS),
-             (64, 64, 384, RUN32, RUN64), (64, 32, 1024, RUN32, LDS)]
-    qs = [("conv",) + k + (0,) for k, _ in known]
-    for k, (cin, cout, runs, _, _) in enumerate(lines + f32):
-        qs += [("conv", 1, runs + more, 128, cin, cout, k >= len(lines)) for more in (0, 1)]
-    want = [w for _, w in known] + [w for line in lines + f32 for w in line[3:]]
+    """Sizes whose fastest kernel is known by a wide margin (times in nn_rules.h),
+    with a bias, with a mask and with neither, and either side of every line."""
+    bias, mask, none, f32 = (1, 0, 0), (0, 1, 0), (0, 0, 0), (0, 0, 1)
+    known = [((8, 512, 64, 256, 128), bias, LDS), ((8, 512, 64, 256, 128), mask, LDS), ((3, 512, 64, 256, 128), mask, LDS),
+             ((16, 64, 64, 384, 128), bias, LDS), ((16, 32, 32, 256, 256), bias, RUN64),
+             ((1, 32, 32, 256, 256), bias, RUN32), ((16, 64, 64, 64, 256), mask, RUN64), ((16, 128, 128, 64, 128), mask, RUN64),
+             ((1, 1024, 64, 512, 64), bias, LDS), ((16, 128, 128, 192, 64), bias, LDS), ((16, 128, 128, 192, 64), mask, RUN64),
+             ((16, 128, 128, 64, 64), mask, RUN64), ((16, 256, 256, 96, 32), bias, LDS), ((8, 128, 128, 128, 32), bias, RUN32),
+             ((1, 32, 32, 64, 64), bias, RUN32), ((16, 256, 256, 32, 32), bias, TILE), ((16, 128, 128, 32, 64), mask, TILE),
+             ((1, 8, 8, 32, 256), bias, TILE)]
+    # inputs, outputs, runs of 128 pixels, options, kernels there and one run on
+    lines = [(128, 128, 640, bias, RUN64, LDS), (128, 128, 768, bias, LDS, RUN64), (128, 128, 1279, mask, RUN64, LDS),
+             (192, 128, 639, bias, RUN64, LDS), (192, 128, 1023, mask, RUN64, LDS), (256, 128, 639, mask, RUN64, LDS),
+             (288, 128, 511, bias, RUN64, LDS), (128, 128, 511, none, RUN64, LDS), (384, 128, 383, none, RUN64, LDS),
+             (64, 128, 640, bias, RUN64, LDS), (64, 128, 768, bias, LDS, RUN64), (64, 128, 1280, none, RUN64, LDS),
+             (64, 128, 192, mask, RUN32, RUN64), (128, 64, 1280, bias, RUN64, LDS), (288, 64, 384, bias, RUN32, LDS),
+             (288, 64, 512, bias, LDS, RUN64), (64, 64, 384, bias, RUN32, RUN64), (64, 64, 1280, f32, RUN64, LDS),
+             (96, 32, 2047, bias, RUN32, LDS)]
+    qs = [("conv",) + k + o for k, o, _ in known]
+    for cin, cout, runs, o, _, _ in lines:
+        qs += [("conv", 1, runs + more, 128, cin, cout) + o for more in (0, 1)]
+    want = [w for _, _, w in known] + [w for line in lines for w in line[4:]]
     got = [int(v[0]) for v in ask(*qs)]
     assert got == want, [(q, g, w) for q, g, w in zip(qs, got, want) if g != w]
 
