@@ -118,7 +118,7 @@ struct BatchLaunch {
     const int *active;      // device: case ids of the active cases
     int parity;             // launches since the table upload, mod 2
     uint32_t fields;        // emitted fields (0: none)
-    int grid;               // blocks of the persistent launch (one and two steps), units of all cases (more)
+    int grid;               // blocks of the persistent launch (one and two steps), march_grid() units (more)
     int steps;              // steps of the launch
     Cover cover;            // units of several steps
     bool gen;               // any case has a force field or runs Scheme II
