@@ -677,8 +677,8 @@ def precision_study(out_path, N=256, steps=(1000, 2500, 5000)):
 
 def batch_study(out_path, ncases=512, max_steps=400000, wall_budget_s=420.0):
     """The seeded uneven batch: 512 cavity/channel cases, N in {64..512},
-    Re log-uniform in [10, 1000], FP32, one persistent launch per step;
-    autotuned launch shape, throughput, then every case run to residual
+    Re log-uniform in [10, 1000], FP32, batched launches; autotuned launch
+    shape, throughput, then every case run to residual
     1e-8 (checked every 100 steps)."""
     import numpy as np
     import torch
@@ -749,7 +749,7 @@ def batch_study(out_path, ncases=512, max_steps=400000, wall_budget_s=420.0):
 def steady_study(out_path):
     """Wall time from initialisation to residual 1e-8 (K = 100) for the
     channel and the cavities of the benchmark configuration (FP32, vorticity
-    and strain rate emitted every step for the cavities)."""
+    and strain rate emitted by every launch for the cavities)."""
     import torch
     from paper_2108_08591_amd import cases as C
     from paper_2108_08591_amd import mdf
