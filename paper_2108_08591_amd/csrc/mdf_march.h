@@ -354,6 +354,11 @@ struct TileShape {
     static constexpr int W = LARGE ? 32 : 16, H = LARGE ? 32 : 16;             // columns and rows
     static constexpr int R = LARGE && sizeof(typename Store<ST>::T) > 2 ? 2 : 1, NT = W * H / R;   // rows per thread, threads
     static constexpr int SX = W - 2 * kTileHalo, SY = H - 2 * kTileHalo;       // nodes written
+    // Wavefronts per SIMD at least: two blocks of 16 fit a CU.  With a mask and
+    // emitted fields 98 to 102 SGPRs would be taken, of which 7 wavefronts fit and
+    // with them one block, and now 78 (21 steps, 2048^2: BF16 D2Q4 1049 and 792 us,
+    // FP16 D2Q5 1004 and 782 us; in launches of two steps 864 and 969).
+    static constexpr int WAVES = NT == 1024 ? 8 : 1;
 };
 
 template <class L, int ST, bool LARGE>
@@ -484,7 +489,7 @@ __device__ __forceinline__ void tile_steps(const KCase &pc, int gx, int tile,
 }
 
 template <class L, int ST, bool LARGE, int K, bool GEN, bool EMIT, bool MASK>
-__global__ void __launch_bounds__((TileShape<ST, LARGE>::NT))
+__global__ void __launch_bounds__((TileShape<ST, LARGE>::NT), (TileShape<ST, LARGE>::WAVES))
 k_tile(KCase p, Tiling tl, const typename Store<ST>::T *__restrict__ src, typename Store<ST>::T *__restrict__ dst,
        const uint8_t *__restrict__ links, uint32_t fields, typename Store<ST>::C *__restrict__ out)
 {
@@ -508,7 +513,7 @@ k_march(KCase p, Tiling tl, MarchGrid g, const typename Store<ST>::T *__restrict
 // k_tile over the flat list of the tiles of a batch's active cases (prefix
 // offsets tile_start2, total meta[2]).
 template <class L, int ST, bool LARGE, int K, bool GEN, bool EMIT, bool MASK>
-__global__ void __launch_bounds__((TileShape<ST, LARGE>::NT))
+__global__ void __launch_bounds__((TileShape<ST, LARGE>::NT), (TileShape<ST, LARGE>::WAVES))
 k_tile_batch(const BatchEntry *__restrict__ tab, const int *__restrict__ meta, const int *__restrict__ tile_start2,
              const int *__restrict__ active, int parity, uint32_t fields, int groups)
 {
