@@ -361,6 +361,16 @@ bool march_form(const mdf_ctx *ctx)
 // Cases that take the kernels with a force field and Scheme II.
 bool general_case(const KCase &p) { return p.ffield != nullptr || p.forcing != MDF_FORCING_PLAIN; }
 
+// Most steps per launch of form 2 over case k.
+int most_steps(const mdf_ctx *ctx, int k, mdf::Cover cover, uint32_t fields)
+{
+    const KCase &p = ctx->kc[k];
+    mdf::MarchWork w{lat_ns(ctx->lattice), lat_planes(ctx->lattice), (long long)p.nx * p.ny,
+                     ctx->bufs[k].links != nullptr, general_case(p), false, fields};
+    for (int f = 0; f < 4; ++f) w.walls = w.walls || p.bc[f] == MDF_WALL;
+    return mdf::march_two(cover, ctx->storage, w) ? 2 : mdf::march_max(cover, ctx->storage, w.mask, w.gen);
+}
+
 // Advance case k by nsteps, several steps (2D) or two (3D) per launch in form
 // 2.  The call always ends with at least one one-step launch, so that the
 // buffer the read kernels pull from holds f*(t - 1) again; the check (if any)
@@ -371,9 +381,9 @@ mdf_status advance_case(mdf_ctx *ctx, int k, int64_t nsteps, bool check_last, ui
     if (march_form(ctx)) {
         const KCase &p = ctx->kc[k];
         const mdf::Cover cover = mdf::march_emit_cover(ctx->cover, fields);
+        const int most = most_steps(ctx, k, cover, fields);
         while (nsteps > 0) {
-            const int n = mdf::march_next(nsteps, mdf::march_max(cover, ctx->storage,
-                                                                 ctx->bufs[k].links != nullptr, general_case(p)));
+            const int n = mdf::march_next(nsteps, most);
             if (n == 1) {
                 nsteps -= 1;
                 mdf_status r = step_case(ctx, k, check_last && nsteps == 0, fields, out, st, nblocks);

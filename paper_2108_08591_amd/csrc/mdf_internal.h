@@ -259,6 +259,30 @@ inline int march_max(Cover cover, int storage, bool mask, bool gen)
     return cover == kCoverStrips && storage == MDF_F32 && !mask && !gen ? 5 : 4;
 }
 
+// What a launch of several steps of one case works on: the stored sets and
+// populations of a node, the nodes, and the fields emitted.
+struct MarchWork {
+    int sets, pops;
+    long long nodes;
+    bool mask, gen, walls;
+    uint32_t fields;
+};
+
+// Whether two steps per launch (k_step2) take less time than march_max in
+// tiles, one case at a time (batches do better in tiles: 4 x 1000^2 FP16 754 and
+// 898 us): for the 16-bit formats with all three sets on periodic grids of more
+// than 3.5 million nodes, still inside the Infinity Cache, where k_step2's rows of
+// 64 nodes read and write whole lines and no halo of 4 is computed again (21
+// steps, us in tiles and in launches of two: BF16 D2Q4 1800^2 550 and 558, 1900^2
+// 619 and 602, 2100^2 757 and 714; FP16 D2Q5 1800^2 535 and 552, 2048^2 691 and
+// 665, between walls 645 and 665; with two sets 2100^2 509 and 532).
+inline bool march_two(Cover cover, int storage, const MarchWork &w)
+{
+    if (cover != kCoverLarge || w.gen) return false;
+    const bool narrow = storage != MDF_F64 && storage != MDF_F32;
+    return narrow && w.sets == 3 && w.nodes > 3500000 && !w.mask && !w.walls && !w.fields;
+}
+
 // Steps of the next launch of a call that has `left` steps to go: 2 .. most, as
 // even as they come, but for the last step, which is a launch of its own, so
 // that the other buffer holds f*(t - 1) for the read kernels (and because the

@@ -253,3 +253,24 @@ def test_longest_launches_in_batches(storage, sizes, n, mask):
         stream.synchronize()
     assert all(torch.isfinite(t).all() for t in out[0])
     assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("storage", ["f16dev", "bf16dev"])
+def test_two_steps_on_large_periodic_grids(storage):
+    """Periodic grids of more than 3.5 million nodes inside the Infinity Cache:
+    two steps per launch, then, between steps that emit, tiles."""
+    nx, ny = 2003, 1801
+    print(f"[gpu] large periodic {storage} {nx}x{ny}", flush=True)
+    out = []
+    for form in (0, 2):
+        s = mdf.Solver(_spec(nx, ny, False, False, None), storage=storage, init=("fields", [_init(nx, ny, storage)]),
+                       u_ref=0.1)
+        s.set_launch(64, 4, 8, form)
+        s.step(4)
+        got = [s.populations()]
+        s.step(9)
+        got += [s.populations()] + s.step_emit(6, MOM)
+        s.step(6)
+        out.append(got + [s.populations()])
+    assert all(torch.isfinite(t).all() for t in out[0])
+    assert all(torch.equal(a, b) for a, b in zip(*out))

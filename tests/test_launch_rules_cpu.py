@@ -41,6 +41,21 @@ def test_five_steps_only_where_the_kernel_keeps_its_registers(ask):
         assert most == (5 if (c, s, m, g) == (STRIPS, mdf.F32, 0, 0) else 4), (c, s, m, g)
 
 
+def test_two_steps_in_plain_16_bit_launches_near_the_cache(ask):
+    """Two steps per launch for all sets of the 16-bit formats in large tiles of
+    more than 3.5 million nodes, without mask, walls, fields and force; tiles
+    of up to four steps elsewhere."""
+    for lattice_pops in ((3, 15), (3, 12), (2, 10), (2, 8)):
+        for c in (STRIPS, SMALL, LARGE):
+            for s in STORAGES:
+                base = [lattice_pops[0], lattice_pops[1], 3500001, 0, 0, 0, 0]
+                others = [base[:i] + [v] + base[i + 1:]
+                          for i, v in ((2, 3500000), (3, 1), (4, 1), (5, 1), (6, mdf.FIELD_VORT))]
+                got = ask(*[("two", c, s, *w) for w in [base] + others])
+                assert got[0] == [c == LARGE and s in (mdf.F16DEV, mdf.BF16DEV) and lattice_pops[0] == 3], (c, s)
+                assert not any(v[0] for v in got[1:]), (c, s)
+
+
 def test_steps_of_a_call(ask):
     """A call's launches take all of its steps, at most `most` each, the last
     one alone, and no others alone but in a call of two: the two steps before
