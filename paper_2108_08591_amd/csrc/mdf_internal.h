@@ -268,6 +268,13 @@ struct MarchWork {
     uint32_t fields;
 };
 
+// Channels of the fields of a 2D case.
+inline int channels_2d(uint32_t fields)
+{
+    return (fields & MDF_FIELD_MOMENTS ? 4 : 0) + (fields & MDF_FIELD_GRAD ? 4 : 0) + (fields & MDF_FIELD_DIV ? 1 : 0) +
+           (fields & MDF_FIELD_STRAIN ? 3 : 0) + (fields & MDF_FIELD_STRESS ? 3 : 0) + (fields & MDF_FIELD_VORT ? 1 : 0);
+}
+
 // Whether two steps per launch (k_step2) take less time than march_max in
 // tiles, one case at a time (batches do better in tiles: 4 x 1000^2 FP16 754 and
 // 898 us): for the 16-bit formats with all three sets on periodic grids of more
@@ -275,12 +282,24 @@ struct MarchWork {
 // 64 nodes read and write whole lines and no halo of 4 is computed again (21
 // steps, us in tiles and in launches of two: BF16 D2Q4 1800^2 550 and 558, 1900^2
 // 619 and 602, 2100^2 757 and 714; FP16 D2Q5 1800^2 535 and 552, 2048^2 691 and
-// 665, between walls 645 and 665; with two sets 2100^2 509 and 532).
+// 665, between walls 645 and 665; with two sets 2100^2 509 and 532); and for
+// FP64 that accumulates many channels, most of what a step then moves, of which
+// tiles of 24 columns share the lines of their edges: more than one and a half
+// per population (21 steps, 16 channels, ms: D2Q4 two sets 512^2 0.289 and 0.251,
+// 1500^2 3.14 and 3.09, 4096^2 24.5 and 21.3, D2Q5 1500^2 3.28 and 3.41, 4096^2 25.9
+// and 23.8; three sets D2Q4 1500^2 3.45 and 3.78, 4096^2 27.1 and 26.8; 4 channels
+// D2Q4 two sets 4096^2 7.29 and 7.82), and ten and more on grids of few tiles per
+// CU, which leave it waiting (us, D2Q5 three sets 16 channels 350^2 252
+// and 217, 420^2 288 and 252, 512^2 317 and 383; 8 channels 350^2 135 and 154).
 inline bool march_two(Cover cover, int storage, const MarchWork &w)
 {
     if (cover != kCoverLarge || w.gen) return false;
-    const bool narrow = storage != MDF_F64 && storage != MDF_F32;
-    return narrow && w.sets == 3 && w.nodes > 3500000 && !w.mask && !w.walls && !w.fields;
+    if (storage == MDF_F64) {
+        const int ch = channels_2d(w.fields);
+        const bool small = w.nodes > 100000 && w.nodes * w.pops <= 3200000;
+        return (w.fields & MDF_FIELD_ACCUMULATE) && (2 * ch > 3 * w.pops || (small && ch >= 10));
+    }
+    return storage != MDF_F32 && w.sets == 3 && w.nodes > 3500000 && !w.mask && !w.walls && !w.fields;
 }
 
 // Steps of the next launch of a call that has `left` steps to go: 2 .. most, as

@@ -16,9 +16,10 @@ int main()
             if (std::scanf("%d%d%d%d", a, a + 1, a + 2, a + 3) != 4) return 1;
             std::printf("%d\n", mdf::march_max(mdf::Cover(a[0]), a[1], a[2] != 0, a[3] != 0));
         } else if (!std::strcmp(what, "two")) {         // cover storage sets pops nodes mask gen walls fields
+            long long n = 0;
             int b = 0;
-            if (std::scanf("%d%d%d%d%d%d%d%d%d", a, a + 1, a + 2, a + 3, a + 4, a + 5, a + 6, a + 7, &b) != 9) return 1;
-            const mdf::MarchWork w{a[2], a[3], a[4], a[5] != 0, a[6] != 0, a[7] != 0, uint32_t(b)};
+            if (std::scanf("%d%d%d%d%lld%d%d%d%d", a, a + 1, a + 2, a + 3, &n, a + 5, a + 6, a + 7, &b) != 9) return 1;
+            const mdf::MarchWork w{a[2], a[3], n, a[5] != 0, a[6] != 0, a[7] != 0, uint32_t(b)};
             std::printf("%d\n", int(mdf::march_two(mdf::Cover(a[0]), a[1], w)));
         } else if (!std::strcmp(what, "next")) {        // left most
             if (std::scanf("%d%d", a, a + 1) != 2) return 1;

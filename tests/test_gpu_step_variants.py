@@ -5,8 +5,8 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2108_08591_amd import mdf
-from test_gpu_several_steps import _spec
+from paper_2108_08591_amd import cases as C, mdf
+from test_gpu_several_steps import _compare, _spec
 
 pytestmark = pytest.mark.gpu
 
@@ -274,3 +274,15 @@ def test_two_steps_on_large_periodic_grids(storage):
         out.append(got + [s.populations()])
     assert all(torch.isfinite(t).all() for t in out[0])
     assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("lattice", [C.D2Q5, mdf.D2Q4])
+@pytest.mark.parametrize("mask", [False, True])
+@pytest.mark.parametrize("steps", [3, 8, 9])
+def test_two_steps_that_accumulate_many_channels(lattice, mask, steps):
+    """FP64, all channels accumulated by two sets and, on a small grid, by three:
+    two steps per launch, after and before launches of up to four."""
+    for nx, ny, sets in ((300, 259, "velocity"), (391, 401, "all")):
+        rng = np.random.default_rng(5)
+        solid = (rng.random((ny, nx)) < 0.1).astype(np.uint8) if mask else None
+        _compare(_spec(nx, ny, mask, False, rng, lattice), "f64", steps, solid, sets=sets, label=sets)

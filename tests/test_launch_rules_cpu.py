@@ -56,6 +56,21 @@ def test_two_steps_in_plain_16_bit_launches_near_the_cache(ask):
                 assert not any(v[0] for v in got[1:]), (c, s)
 
 
+def test_two_steps_where_fp64_accumulates_many_channels(ask):
+    """Two steps per launch in FP64 large tiles where more than one and a half
+    channels per population are accumulated, or ten and more on small grids."""
+    channels = {mdf.FIELD_MOMENTS: 4, mdf.FIELD_GRAD: 4, mdf.FIELD_DIV: 1, mdf.FIELD_STRAIN: 3, mdf.FIELD_STRESS: 3,
+                mdf.FIELD_VORT: 1}
+    qs = [(c, s, sets, pops, nodes, m, g, wall, f | acc) for c in (STRIPS, SMALL, LARGE) for s in (mdf.F64, mdf.F32)
+          for sets, pops in ((3, 15), (3, 12), (2, 10), (2, 8)) for m, g, wall in ((0, 0, 0), (1, 0, 1), (0, 1, 0))
+          for nodes in (100000, 100001, 3200000 // pops, 3200000 // pops + 1, 2 ** 31)
+          for f in range(mdf.FIELD_ALL + 1) for acc in (0, mdf.FIELD_ACCUMULATE)]
+    for (c, s, sets, pops, nodes, m, g, wall, f), (two,) in zip(qs, ask(*[("two",) + q for q in qs])):
+        n = sum(v for bit, v in channels.items() if f & bit)
+        many = n > 1.5 * pops or (n >= 10 and 100000 < nodes <= 3200000 // pops)
+        assert two == (c == LARGE and s == mdf.F64 and not g and bool(f & mdf.FIELD_ACCUMULATE) and many)
+
+
 def test_steps_of_a_call(ask):
     """A call's launches take all of its steps, at most `most` each, the last
     one alone, and no others alone but in a call of two: the two steps before
